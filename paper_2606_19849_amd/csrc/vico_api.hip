@@ -184,6 +184,35 @@ int check_gather_shape(int32_t Lq, int32_t T, int32_t S, int32_t cap, int32_t n_
   return VICO_OK;
 }
 
+// Row tiles and key-range parts of the rows kernel (attn_rows.hip) for NR
+// packed rows per KV head and about `keys` keys, and their cost in key blocks
+// that one work-group walks: rounds * (start + blocks per part), plus the merge.
+// A block of 32 keys takes a work-group about 0.28 us at head_dim 128 (a CU
+// streams at most ~57 GB/s) and 0.17 us at 64, 5-10 % more with two row blocks;
+// the start (table, Q, first keys, the waves' merge) and the merge launch each
+// take about as long as 14 blocks.
+struct RowsPlan { int row_blocks, n_rt, parts; int64_t part_blocks, cost; };
+constexpr int64_t kRowsStart = 14;
+constexpr int64_t kRowsChunkCost = 84;       // chunk prefill: the rows kernel up to this cost
+
+RowsPlan plan_rows(int64_t NR, int Hkv, int64_t keys, int max_parts, int exact_parts) {
+  RowsPlan best{};
+  const int64_t blocks = (keys + vico::kRowsBlock - 1) / vico::kRowsBlock;
+  for (int rb = 1; rb <= 2; ++rb) {
+    RowsPlan p;
+    p.row_blocks = rb;
+    p.n_rt = (int)((NR + 16 * rb - 1) / (16 * rb));
+    const int64_t base = int64_t(Hkv) * p.n_rt;
+    p.parts = exact_parts > 0 ? exact_parts
+                              : (int)std::max<int64_t>(1, std::min<int64_t>(max_parts, vico::kNumCUs / base));
+    const int64_t rounds = (base * p.parts + vico::kNumCUs - 1) / vico::kNumCUs;
+    p.part_blocks = (blocks + p.parts - 1) / p.parts;
+    p.cost = rounds * (kRowsStart + p.part_blocks * (rb == 2 ? 11 : 10) / 10) + (p.parts > 1 ? kRowsStart : 0);
+    if (rb == 1 || p.cost < best.cost) best = p;
+  }
+  return best;
+}
+
 bool aligned_to(const void* p, uintptr_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; }
 
 int hip_fail(hipError_t e) {
@@ -338,6 +367,35 @@ int vico_chunk_prefill_attn_ex(const void* q, const void* k_chunk, const void* v
   }
   const double scale = softmax_scale > 0.f ? double(softmax_scale) : 1.0 / sqrt(double(head_dim));
   a.scale_log2 = (float)(scale * 1.4426950408889634);
+  // Small chunks over short key ranges take the rows kernel: a 256-row tile
+  // leaves most CUs idle there and walks its keys alone.  The line (about 24
+  // us at head_dim 128) lies where the two meet; measured without append, us
+  // per call, rows against tile kernel: 3B heads, 48 tokens, window 256 8.1 /
+  // 19.1, 1024 14.4 / 24.8; 512 tokens, 1024 20.8 / 28.9 (cost 70), 3000
+  // 40.3 / 33.3 (cost 137); 7B heads, 512 tokens, 256 (two rounds, cost 84)
+  // 24.9 / 29.2; 307 tokens, 1024 (two rounds, cost 124) 34.4 / 31.5.  A split
+  // that the caller chose stays with the tile kernel.
+  const RowsPlan rp = plan_rows(int64_t(sh.Hq / sh.Hkv) * sh.C, sh.Hkv, int64_t(sh.S) + sh.Wv + sh.C, sh.splits, 0);
+  if (num_splits == 0 && rp.cost <= kRowsChunkCost) {
+    vico::RowsArgs r{};
+    r.q = a.q; r.tail_k = a.kc; r.tail_v = a.vc; r.sink_k = a.sink_k; r.sink_v = a.sink_v;
+    r.store_k = a.ring_k; r.store_v = a.ring_v;
+    r.out = a.out; r.lse = a.lse; r.ws_o = a.ws_o; r.ws_lse = a.ws_lse;
+    r.Lq = r.T = a.C; r.S = a.S; r.cap = a.R; r.n_segs = 2;
+    r.seg0 = a.ws; r.len0 = std::min(a.Wv, a.R - a.ws); r.len1 = a.Wv - r.len0;
+    r.Hq = a.Hq; r.Hkv = a.Hkv; r.D = a.D;
+    r.parts = rp.parts; r.n_rt = rp.n_rt; r.row_blocks = rp.row_blocks;
+    r.out_f32 = a.out_f32; r.bidir = a.bidir; r.scale_log2 = a.scale_log2;
+    hipError_t e = vico::launch_rows(r, (hipStream_t)stream);
+    if (e == hipSuccess && rp.parts > 1) {
+      a.splits = rp.parts;
+      e = vico::launch_merge(a, (hipStream_t)stream);          // appends too, when asked
+    } else if (e == hipSuccess && append) {
+      const vico::AppendArgs ap{a.kc, a.vc, a.app_rk, a.app_rv, a.C, a.R, a.app_p0, a.Hkv * a.D};
+      e = vico::launch_append(ap, (hipStream_t)stream);
+    }
+    return e == hipSuccess ? VICO_OK : hip_fail(e);
+  }
   const hipError_t e = vico::launch_attention(a, sh.grid, (hipStream_t)stream);
   return e == hipSuccess ? VICO_OK : hip_fail(e);
 }
@@ -525,7 +583,38 @@ int vico::gather_attn_entry(const void* q, int32_t q_len, const void* tail_k, co
   a.out_f32 = out_dtype == VICO_DTYPE_F32;
   const double scale = softmax_scale > 0.f ? double(softmax_scale) : 1.0 / sqrt(double(head_dim));
   a.scale_log2 = (float)(scale * 1.4426950408889634);
-  const hipError_t e = vico::launch_gather(a, (hipStream_t)stream);
+  // The rows kernel takes tables of up to 64 entries where its work-groups'
+  // key ranges are short: each row tile streams the keys for itself, while
+  // the 256-row kernel reads them once for all rows.  Measured with 32 chunks
+  // (20.5k keys, 7B heads), us per call, rows against 256-row kernel: 7 rows
+  // 16.6 / 22.6, 56 rows 20.9 / 26.5, 112 rows (40 blocks a part) 26.6 / 28.6,
+  // 168 rows (64 blocks) 34.0 / 32.9; 3B heads, 384 rows (64 blocks, two tiles
+  // of the 256-row kernel) 30.1 / 33.9.
+  hipError_t e;
+  const int64_t rows = int64_t(sh.Hq / sh.Hkv) * sh.Lq;
+  const RowsPlan rp = plan_rows(rows, sh.Hkv, int64_t(sh.S) + std::min<int64_t>(keys_hint, kMaxKeys) + sh.T, sh.parts,
+                                num_splits > 0 ? sh.parts : 0);
+  if (sh.n_segs <= vico::kRowsMaxSegments && (rp.n_rt == 1 || rp.part_blocks <= (rows > 256 ? 72 : 56))) {
+    vico::RowsArgs r{};
+    r.q = a.q; r.tail_k = a.tail_k; r.tail_v = a.tail_v; r.sink_k = a.sink_k; r.sink_v = a.sink_v;
+    r.store_k = a.store_k; r.store_v = a.store_v; r.seg_start = a.seg_start; r.seg_len = a.seg_len;
+    r.out = a.out; r.lse = a.lse; r.ws_o = a.ws_o; r.ws_lse = a.ws_lse;
+    r.Lq = a.Lq; r.T = a.T; r.S = a.S; r.cap = a.cap; r.n_segs = a.n_segs;
+    r.Hq = a.Hq; r.Hkv = a.Hkv; r.D = a.D;
+    r.parts = rp.parts; r.n_rt = rp.n_rt; r.row_blocks = rp.row_blocks;
+    r.out_f32 = a.out_f32; r.scale_log2 = a.scale_log2;
+    if (a.n_segs == 0) r.seg_start = nullptr;
+    e = vico::launch_rows(r, (hipStream_t)stream);
+    if (e == hipSuccess && r.parts > 1) {
+      vico::AttnArgs m{};
+      m.out = a.out; m.lse = a.lse; m.ws_o = a.ws_o; m.ws_lse = a.ws_lse;
+      m.C = a.Lq; m.Hq = a.Hq; m.Hkv = a.Hkv; m.D = a.D;
+      m.splits = r.parts; m.out_f32 = a.out_f32;
+      e = vico::launch_merge(m, (hipStream_t)stream);
+    }
+  } else {
+    e = vico::launch_gather(a, (hipStream_t)stream);
+  }
   return e == hipSuccess ? VICO_OK : hip_fail(e);
 }
 

@@ -78,6 +78,34 @@ struct GatherArgs {
   float scale_log2;
 };
 
+// Few query rows, keys read straight into registers (attn_rows.hip): row
+// tiles of 16 * row_blocks packed rows, the key range in `parts`.  Keys as in
+// GatherArgs; the store segments come from a device table (seg_start,
+// seg_len) or, with seg_start null, are the two slot ranges of a ring window.
+constexpr int kRowsBlock = 32;         // keys per block
+constexpr int kRowsMaxSegments = 64;   // table entries (one per lane)
+struct RowsArgs {
+  const uint16_t* q;
+  const uint16_t* tail_k;
+  const uint16_t* tail_v;
+  const uint16_t* sink_k;
+  const uint16_t* sink_v;
+  const uint16_t* store_k;
+  const uint16_t* store_v;
+  const int64_t* seg_start;
+  const int32_t* seg_len;
+  void* out;
+  float* lse;               // may be null
+  float* ws_o;              // [parts][Hq][Lq][D] fp32 when parts > 1
+  float* ws_lse;            // [parts][Hq][Lq] (log2 units)
+  int Lq, T, S, cap, n_segs;
+  int seg0, len0, len1;     // seg_start null: slots [seg0, seg0 + len0) and [0, len1)
+  int Hq, Hkv, D;
+  int parts, n_rt, row_blocks;
+  int out_f32, bidir;
+  float scale_log2;
+};
+
 struct AppendArgs {
   const uint16_t* kc;
   const uint16_t* vc;
@@ -113,6 +141,8 @@ hipError_t launch_attention(const AttnArgs& a, int grid, hipStream_t stream);
 hipError_t launch_merge(const AttnArgs& a, hipStream_t stream);
 hipError_t launch_append(const AppendArgs& a, hipStream_t stream);
 hipError_t launch_gather(const GatherArgs& a, hipStream_t stream);
+// The rows kernel alone; the caller merges when parts > 1.
+hipError_t launch_rows(const RowsArgs& a, hipStream_t stream);
 // Records e as the calling thread's last HIP error; returns VICO_ERR_HIP.
 int record_hip_failure(hipError_t e);
 

@@ -1,0 +1,110 @@
+"""The register-streamed rows kernel (small chunks, decode steps, short
+queries) and the pipelined tile kernel at the sizes where they can go wrong:
+edges of 16- and 32-row tiles, of 32-key blocks and 64-key tiles, ranges
+shorter than the pipeline, blocks across segments.  Reference: the fp64 oracle
+with the derived per-element bound; and the same call on the other kernel,
+each within its bound."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2606_19849_amd as vico
+from synth import ChunkShape, QueryShape, make_chunk_inputs, make_query_inputs
+from tests._gpu import DeviceChunk, check_bf16, check_f32, oracle_and_bound
+from tests.test_gpu_retrieval import DeviceQuery
+
+pytestmark = pytest.mark.gpu
+
+
+# heads, kv heads, d, sink, ring, history, window, chunk: packed rows g*C around 16 and 32, keys
+# around multiples of 32, no history, one token, wrapped ring
+ROWS_CHUNKS = [
+    (4, 4, 64, 0, 64, 0, 0, 1),
+    (4, 4, 128, 0, 64, 31, 31, 1),
+    (8, 1, 128, 1, 40, 90, 30, 2),
+    (7, 1, 128, 16, 80, 177, 64, 5),
+    (8, 2, 64, 32, 128, 300, 128, 8),
+    (16, 2, 128, 5, 200, 333, 187, 33),
+    (6, 2, 128, 64, 96, 100, 96, 11),
+    (3, 3, 64, 3, 500, 1203, 467, 65),
+    (28, 4, 128, 64, 700, 2000, 612, 77),
+]
+
+
+@pytest.mark.parametrize("case", range(len(ROWS_CHUNKS)))
+@pytest.mark.parametrize("flags", [0, vico.VICO_ATTN_BIDIRECTIONAL])
+def test_small_chunks_on_both_kernels(case, flags):
+    """The planner's choice (the rows kernel here) and the tile kernel (a split
+    count given by the caller) against the oracle, fp32 and bf16 results."""
+    inp = make_chunk_inputs(ChunkShape(*ROWS_CHUNKS[case]), seed=700 + case, family="F2")
+    dc = DeviceChunk(inp)
+    for splits in (0, 1, 3):
+        o, lse = dc.attention(torch.float32, num_splits=splits, flags=flags)
+        ref, ref_lse, b = oracle_and_bound(inp, parts=max(dc.parts, 8), bidirectional=bool(flags))
+        check_f32(o, ref, b, lse, ref_lse)
+        check_bf16(dc.attention(torch.bfloat16, num_splits=splits, flags=flags)[0], ref, b)
+
+
+def _table(rng, n_seg, cap):
+    """Segments of 0 to 70 keys in scattered order, some reaching outside the store."""
+    st = rng.integers(-20, cap, n_seg)
+    ln = rng.integers(-2, 71, n_seg)
+    return st.astype(np.int64), ln.astype(np.int32)
+
+
+@pytest.mark.parametrize("heads", [(8, 2, 128), (7, 1, 128), (4, 4, 64), (12, 2, 64)])
+@pytest.mark.parametrize("q_len,tail", [(1, 1), (2, 31), (4, 4), (5, 40), (9, 9), (33, 64)])
+@pytest.mark.parametrize("n_seg", [0, 1, 7, 64])
+def test_gathered_rows(heads, q_len, tail, n_seg):
+    """Tables of up to 64 entries take the rows kernel; the same table padded
+    with empty entries to 65 takes the 256-row kernel."""
+    Hq, Hkv, D = heads
+    sh = QueryShape(Hq, Hkv, D, 19, 64, 12, 20, 90, q_len, tail, 6)
+    qi = make_query_inputs(sh, seed=900 + q_len + n_seg, family="F2")
+    d = DeviceQuery(qi)
+    st, ln = _table(np.random.default_rng(31 * q_len + n_seg), n_seg, qi.store_len)
+    lo = np.clip(st, 0, qi.store_len)
+    hi = np.clip(st + ln, 0, qi.store_len)
+    keep = hi > lo
+    pad = 65 - n_seg
+    wide = (np.concatenate([st, np.zeros(pad, np.int64)]), np.concatenate([ln, np.zeros(pad, np.int32)]))
+    for splits in (0, 3):
+        for table in ((st, ln), wide):
+            o, lse, parts = d.attend(*table, num_splits=splits)
+            ro, rl, b = d.reference(lo[keep], (hi - lo)[keep], parts=max(parts, 8))
+            check_f32(o, ro, b, lse, rl)
+
+
+# key ranges of one to six 64-key tiles per split (the pipeline runs three tiles ahead), row counts
+# around a wave's 32 rows and a work-group's 256, ring end and chunk end inside a tile
+TILE_CHUNKS = [
+    (2, 2, 128, 0, 64, 0, 0, 64, 1),
+    (2, 2, 64, 0, 64, 64, 64, 65, 1),
+    (4, 2, 128, 16, 300, 777, 250, 33, 5),
+    (2, 1, 128, 64, 200, 456, 192, 257, 16),
+    (8, 2, 128, 70, 1000, 4321, 1000, 300, 12),
+    (8, 2, 64, 1, 513, 1500, 512, 255, 7),
+    (4, 1, 128, 64, 640, 1280, 640, 256, 3),
+]
+
+
+@pytest.mark.parametrize("case", range(len(TILE_CHUNKS)))
+@pytest.mark.parametrize("flags", [0, vico.VICO_ATTN_BIDIRECTIONAL])
+def test_tile_kernel_short_ranges(case, flags):
+    """Split counts that leave each work-group one to a few key tiles.  The
+    workspace is filled with NaN patterns first: every partial that the merge
+    reads has been written."""
+    *shape, splits = TILE_CHUNKS[case]
+    inp = make_chunk_inputs(ChunkShape(*shape), seed=800 + case, family="F2")
+    sh = inp.shape
+    dc = DeviceChunk(inp)
+    parts, wb = vico.vico_attn_plan(sh.chunk_len, sh.sink_len, sh.ring_slots, sh.hist_len, sh.window, sh.num_q_heads,
+                                    sh.num_kv_heads, sh.head_dim, splits, flags)
+    ws = torch.full((max(wb, 16),), 255, dtype=torch.uint8, device="cuda")
+    out = torch.empty((sh.chunk_len, sh.num_q_heads, sh.head_dim), dtype=torch.float32, device="cuda")
+    lse = torch.empty((sh.num_q_heads, sh.chunk_len), dtype=torch.float32, device="cuda")
+    vico.vico_chunk_prefill_attn(dc.q, dc.kc, dc.vc, dc.sk, dc.sv, dc.rk, dc.rv, sh.hist_len, sh.window, out, lse=lse,
+                                 workspace=ws, num_splits=splits, flags=flags)
+    torch.cuda.synchronize()
+    ref, ref_lse, b = oracle_and_bound(inp, parts=parts, bidirectional=bool(flags))
+    check_f32(out.cpu().numpy().astype(np.float64), ref, b, lse.cpu().numpy().astype(np.float64), ref_lse)

@@ -159,7 +159,7 @@ struct WaveTile {
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int kk = k0h + 8 * (v >> 2) + hh * 4 + (v & 3);
-      if (kk > key_lim) s[v] = -INFINITY;
+      s[v] = kk > key_lim ? -INFINITY : s[v];
     }
   }
 

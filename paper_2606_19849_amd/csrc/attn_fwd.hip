@@ -18,20 +18,17 @@
 //     instead.  Both forms read the same K/V; the packed one is its own
 //     kernel, attn_fwd_packed_kernel.
 //   * The tile body (S^T = K Q^T and O^T = V^T P^T on v_mfma_f32_32x32x16_bf16,
-//     the exponentiate-first online softmax, two 32-key halves) is WaveTile
-//     of attn_common.h, shared with the gathered-query kernel.
-//   * K/V tiles: 64 keys, double-buffered in LDS; the next tile's loads
-//     are in flight while the current tile is multiplied.  Loads go through
-//     buffer resources (one per sink / ring / chunk tensor): a tile that lies
-//     inside one segment (and does not cross the ring end) is addressed as a
-//     scalar tile base plus a fixed per-thread offset; the few tiles that
-//     straddle a boundary resolve each key row (ring slot = ws + k, minus R
-//     once past the end) and read all three resources with out-of-range
-//     offsets for the wrong ones, which the hardware returns as zero.  Keys
-//     past the chunk end read as zero the same way.  No copies are made.
+//     the exponentiate-first online softmax, software-pipelined over 32-key
+//     halves) is PipeTile of attn_pipe.h.
+//   * K/V tiles: 64 keys, four buffers each in LDS, loaded three tiles ahead
+//     with one barrier per tile.  Loads go straight to LDS through buffer
+//     resources: consecutive tiles inside one tensor (a run) share the
+//     resource and advance a scalar offset; a tile that straddles two tensors
+//     or the ring end resolves each key row (ring slot = ws + k, minus R once
+//     past the end) and loads each tensor's rows with the other lanes switched
+//     off.  Keys past the chunk end read as zero (out of range).  No copies.
 //   * Causal chunk: only tiles that reach past the first row of a wave run the
-//     masked variant of the tile body; tiles beyond the last row of a wave are
-//     skipped by that wave.  With the bidirectional option (Eq. (4) read
+//     mask on their logits.  With the bidirectional option (Eq. (4) read
 //     literally: a chunk sees all of itself) every row's last key is the
 //     chunk's last key, so only the tile holding the chunk end is masked.
 //   * Work-groups are renumbered so that consecutive logical ids (the query
@@ -43,6 +40,7 @@
 #include <type_traits>
 
 #include "attn_common.h"
+#include "attn_pipe.h"
 
 namespace vico {
 namespace {
@@ -51,43 +49,36 @@ namespace {
 // into one kernel per row form (attn_fwd_kernel, attn_fwd_packed_kernel).
 template <int D, bool PACKED>
 __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int gq) {
+  constexpr int RB = kRowBlocks;
+  typedef PipeTile<D, RB> Tile;
   constexpr int BN = kKeyTile;         // keys per tile
   constexpr int BM = kBlockM;          // rows per work-group
-  static_assert(kRowBlocks == 1, "one 32-row block per wave (the shared tile body)");
+  constexpr int NW = kThreads / 64;          // waves per work-group
   // LDS tiles: dense rows of 2*D bytes (the direct loads below write each
   // wave's 64 x 16 bytes contiguously), units swizzled as the tile body reads them
-  constexpr int UPR = D / 8;           // 16-byte units per row
+  constexpr int UPR = Tile::UPR;       // 16-byte units per row
   constexpr int RBY = D * 2;           // bytes per LDS row
-  constexpr int KT = BN * D;           // elements of one K (or V) tile
-  constexpr int VT = BN * D;
-  constexpr int NW = kThreads / 64;          // waves per work-group
-  constexpr int NLD = BN * RBY / 1024 / NW;  // direct 1 KiB loads per wave per tile (K or V)
+  constexpr uint32_t TBY = BN * RBY;         // bytes of one K (or V) tile
+  constexpr int NLD = TBY / 1024 / NW;       // direct 1 KiB loads per wave per tile (K or V)
   constexpr int RPL = 1024 / RBY;            // rows per direct load
-  constexpr int NBUF = kBuffers;
-  static_assert(NLD * NW * 1024 == BN * RBY, "direct loads cover the tile");
-  static_assert(BM == NW * 32, "work-group rows");
-  static_assert(NBUF == 2 || NBUF == 3, "two or three LDS buffers");
-  static_assert(BN % 64 == 0, "key tiles are whole 64-key sub-tiles");
+  constexpr int NDB = Tile::NDB, NKS = Tile::NKS;
+  static_assert(NLD * NW * 1024 == TBY, "direct loads cover the tile");
+  static_assert(BM == NW * RB * 32, "work-group rows");
+  static_assert(BN == 64, "two 32-key halves per tile");
 
-  // NBUF K/V buffers: tile t lives in buffer t mod NBUF and is loaded NBUF-1
-  // tiles ahead.  Separate arrays let the compiler see that reads of one
-  // buffer do not wait for the direct loads landing in another.
-  __shared__ __attribute__((aligned(16))) uint16_t k_lds0[KT], k_lds1[KT], k_lds2[NBUF > 2 ? KT : 1];
-  __shared__ __attribute__((aligned(16))) uint16_t v_lds0[VT], v_lds1[VT], v_lds2[NBUF > 2 ? VT : 1];
-  auto kbuf = [&](auto b) __attribute__((always_inline)) -> uint16_t* {
-    if constexpr (decltype(b)::value == 0) return k_lds0;
-    else if constexpr (decltype(b)::value == 1) return k_lds1;
-    else return k_lds2;
-  };
-  auto vbuf = [&](auto b) __attribute__((always_inline)) -> uint16_t* {
-    if constexpr (decltype(b)::value == 0) return v_lds0;
-    else if constexpr (decltype(b)::value == 1) return v_lds1;
-    else return v_lds2;
-  };
+  // Tile t (counted from the segment's first) lives in K and V buffer t mod NB.
+  // The pipelined body multiplies V one half after K, so with one barrier per
+  // tile the loads run NB - 1 = AHEAD tiles ahead.  One array and one address
+  // register per fragment kind, advanced once per tile: the direct loads are
+  // assembly, so the compiler has no loads in flight to confuse with the reads.
+  constexpr int NB = kBuffers, AHEAD = NB - 1;
+  constexpr uint32_t kKBase = NB * TBY;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * NB * TBY];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void*)lds;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31;
   const int hh = lane >> 5;
   const int C = a.C, S = a.S, SW = a.S + a.Wv;
@@ -118,204 +109,301 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int g
   const int row0 = rt * BM;
   const int n_tiles = tiles_of(rt);
 
-  // this wave: packed rows wrow0 + l32; this lane: token tok of head h
-  const int wrow0 = row0 + wave * 32;
+  // this wave: packed rows wrow0 .. wrow0 + 63 in two blocks; this lane: token
+  // tok[rb] of head h[rb] in each block
+  const int wrow0 = row0 + wave * (RB * 32);
   const bool wave_active = wrow0 < NR;
   const int wave_first_lim = last_key_of_tok(tok_of(wrow0));      // last key of the wave's first row
-  const int wave_last_lim = last_key_of_tok(tok_of(wrow0 + 31));
-  const int my_row = min(wrow0 + l32, NR - 1);
-  const int tok = my_row / P;
-  const int h = h0 + my_row % P;
-  const int key_lim = last_key_of_tok(tok);
+  int tok[RB], h[RB], key_lim[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int r = min(wrow0 + rb * 32 + l32, NR - 1);
+    tok[rb] = r / P;
+    h[rb] = h0 + r % P;
+    key_lim[rb] = last_key_of_tok(tok[rb]);
+  }
 
   // ---- the wave's Q rows and running state.  The Q loads are unconditional:
   // rows past the group's end repeat its last row (the clamped address) and
   // are never stored, and a row's softmax only mixes the two lanes of that row.
-  bf16x8 qf[WaveTile<D>::NKS];
-  WaveTile<D>::load_q(qf, a.q + ((int64_t)tok * a.Hq + h) * D + hh * 8);
+  bf16x8 qf[RB][NKS];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) WaveTile<D>::load_q(qf[rb], a.q + ((int64_t)tok[rb] * a.Hq + h[rb]) * D + hh * 8);
 
-  // ---- tile loader.  Direct load n of wave w fills LDS rows w*BN/4 + n*RPL ..
-  // (RPL rows): lane i writes unit i % UPR of row w*BN/4 + n*RPL + i / UPR and
-  // fetches the logical unit that belongs there under the swizzle.
+  // ---- tile loader.  Direct load n of wave w fills chunk w*NLD + n of the tile
+  // (RPL rows); the layout says which row and unit each lane fetches.  The
+  // byte offset is counted from the tile's first row, less n * 1024: a load's
+  // immediate offset counts on both sides, in LDS (where load n belongs
+  // n * 1024 further on) and in memory.  Not negative: row n * RPL starts at
+  // least n * 1024 bytes into the tile.
   const int rbytes = a.Hkv * D * 2;                            // bytes per token row in HBM
-  const rsrc_t rs_sk = make_rsrc(a.sink_k, S * rbytes), rs_sv = make_rsrc(a.sink_v, S * rbytes);
-  const rsrc_t rs_rk = make_rsrc(a.ring_k, a.R * rbytes), rs_rv = make_rsrc(a.ring_v, a.R * rbytes);
-  const rsrc_t rs_ck = make_rsrc(a.kc, C * rbytes), rs_cv = make_rsrc(a.vc, C * rbytes);
-  int ld_row[NLD];                // tile row filled by this lane in load n
-  uint32_t ld_ck[NLD], ld_cv[NLD];  // byte offset of the fetched K / V unit inside a token row
+  auto k_row = [&](int n, int& unit) __attribute__((always_inline)) {
+    int row;
+    Tile::k_source(wave * NLD + n, lane, row, unit);
+    return (wave * NLD + n) * RPL + row;
+  };
+  auto v_row = [&](int n, int& unit) __attribute__((always_inline)) {
+    int row;
+    Tile::v_source(lane, row, unit);
+    return (wave * NLD + n) * RPL + row;
+  };
+  uint32_t ld_k[NLD], ld_v[NLD];
 #pragma unroll
   for (int n = 0; n < NLD; ++n) {
-    const int r = wave * (BN / NW) + n * RPL + lane / UPR;
-    const int pu = lane % UPR;
-    ld_row[n] = r;
-    ld_ck[n] = (uint32_t)(kv * D * 2 + (pu ^ lds_swz_k<D>(r)) * 16);
-    ld_cv[n] = (uint32_t)(kv * D * 2 + (pu ^ lds_swz_v<D>(r)) * 16);
+    int unit;
+    const int rk = k_row(n, unit);
+    ld_k[n] = (uint32_t)(rk * rbytes + kv * D * 2 + unit * 16 - n * 1024);
+    const int rv = v_row(n, unit);
+    ld_v[n] = (uint32_t)(rv * rbytes + kv * D * 2 + unit * 16 - n * 1024);
   }
 
-  // tile kind (wave-uniform): 0 sink, 1 ring without wrap, 2 chunk, all rows
-  // inside the tensor; 3 anything else (segment boundary, ring end, chunk end)
-  auto tile_mode = [&](int t, int& row_base) __attribute__((always_inline)) {
-    const int k0 = t * BN, k1 = k0 + BN;
-    row_base = 0;
-    if (k1 <= S) { row_base = k0; return 0; }
-    if (k0 >= SW && k1 <= SW + C) { row_base = k0 - SW; return 2; }
-    if (k0 >= S && k1 <= SW) {
+  // A run of tiles that lie in one tensor, without a ring end: their loads
+  // share the two buffer resources and differ in the scalar offset.  run_left
+  // counts the tiles left in it.  A tile across a boundary (mixed) is a run
+  // of one with empty resources (its direct loads then read nothing), to be
+  // filled by load_tile_rows; past the segment's last tile the run is empty
+  // and endless, so every step issues the same number of loads.
+  u32x4 run_k, run_v;
+  uint32_t run_so;
+  int run_left;
+  bool mixed;
+  auto start_run = [&](int t) __attribute__((always_inline)) {
+    const int k0 = t * BN;
+    const uint16_t *bk = a.kc, *bv = a.vc;
+    int rows = 0, row0 = 0, n = 1;           // tensor rows, the tile's first row, tiles in the run
+    mixed = false;
+    if (t >= t_hi) {
+      n = 1 << 30;
+    } else if (k0 + BN <= S) {
+      bk = a.sink_k; bv = a.sink_v;
+      rows = S; row0 = k0;
+      n = (S - k0) / BN;
+    } else if (k0 >= SW && k0 + BN <= SW + C) {
+      rows = C; row0 = k0 - SW;
+      n = (SW + C - k0) / BN;
+    } else {
       int slot0 = a.ws + (k0 - S);
       if (slot0 >= a.R) slot0 -= a.R;
-      if (slot0 + BN <= a.R) { row_base = slot0; return 1; }
-    }
-    return 3;
-  };
-
-  // fast tiles: asynchronous direct loads into LDS buffer `buf`
-  auto load_tile_direct = [&](auto buf, int mode, int row_base) __attribute__((always_inline)) {
-    uint16_t* Ks = kbuf(buf);
-    uint16_t* Vs = vbuf(buf);
-    const uint16_t* bk = mode == 0 ? a.sink_k : (mode == 1 ? a.ring_k : a.kc);
-    const uint16_t* bv = mode == 0 ? a.sink_v : (mode == 1 ? a.ring_v : a.vc);
-    const int nb = mode == 0 ? S * rbytes : (mode == 1 ? a.R * rbytes : C * rbytes);
-    const rsrc_t rk_ = make_rsrc(bk, nb), rv_ = make_rsrc(bv, nb);
-#pragma unroll
-    for (int n = 0; n < NLD; ++n) {
-      const uint32_t rowoff = (uint32_t)(row_base + ld_row[n]) * (uint32_t)rbytes;
-      lds_void* kd = (lds_void*)(Ks + (wave * (BN / NW) + n * RPL) * D);
-      lds_void* vd = (lds_void*)(Vs + (wave * (BN / NW) + n * RPL) * D);
-      load_lds16(rk_, kd, rowoff + ld_ck[n]);
-      load_lds16(rv_, vd, rowoff + ld_cv[n]);
-    }
-  };
-
-  // other tiles: resolve each key row, read all three tensors (out-of-range
-  // offsets return zero), combine, and write the same LDS units.  Synchronous.
-  auto load_tile_rows = [&](auto buf, int t) __attribute__((always_inline)) {
-    uint16_t* Ks = kbuf(buf);
-    uint16_t* Vs = vbuf(buf);
-    const int k0 = t * BN;
-#pragma unroll
-    for (int n = 0; n < NLD; ++n) {
-      const int kk = k0 + ld_row[n];
-      int slot = a.ws + (kk - S);
-      if (slot >= a.R) slot -= a.R;
-      const uint32_t o_s = kk < S ? (uint32_t)kk * rbytes : kOutOfRange;
-      const uint32_t o_r = (kk >= S && kk < SW) ? (uint32_t)slot * rbytes : kOutOfRange;
-      const uint32_t o_c = kk >= SW ? (uint32_t)(kk - SW) * rbytes : kOutOfRange;
-      const u32x4 kx = __builtin_amdgcn_raw_buffer_load_b128(rs_sk, o_s + ld_ck[n], 0, 0) |
-                       __builtin_amdgcn_raw_buffer_load_b128(rs_rk, o_r + ld_ck[n], 0, 0) |
-                       __builtin_amdgcn_raw_buffer_load_b128(rs_ck, o_c + ld_ck[n], 0, 0);
-      const u32x4 vx = __builtin_amdgcn_raw_buffer_load_b128(rs_sv, o_s + ld_cv[n], 0, 0) |
-                       __builtin_amdgcn_raw_buffer_load_b128(rs_rv, o_r + ld_cv[n], 0, 0) |
-                       __builtin_amdgcn_raw_buffer_load_b128(rs_cv, o_c + ld_cv[n], 0, 0);
-      const int pos = ld_row[n] * D + (lane % UPR) * 8;
-      *(u32x4*)(Ks + pos) = kx;
-      *(u32x4*)(Vs + pos) = vx;
-    }
-  };
-
-  // returns true when the tile went out as asynchronous direct loads
-  auto load_tile = [&](auto buf, int t) __attribute__((always_inline)) {
-    int row_base;
-    const int mode = tile_mode(t, row_base);
-    if (mode != 3) {
-      load_tile_direct(buf, mode, row_base);
-      return true;
-    }
-    load_tile_rows(buf, t);
-    return false;
-  };
-
-  uint32_t k_rd[WaveTile<D>::NKS], v_rd[WaveTile<D>::NDB];
-  f32x16 o[WaveTile<D>::NDB];
-  float m_run, l_run, neg_m;
-  WaveTile<D>::start(k_rd, v_rd, o, m_run, l_run, neg_m);
-  WaveTile<D> wt{qf, k_rd, v_rd, o, m_run, l_run, neg_m, a.scale_log2};
-
-  // ---- key loop over the buffers: tile t + NBUF - 1 is loaded while tile t is
-  // multiplied; one barrier per tile.
-  constexpr uint32_t kWaitNewestTile = 0x0F70u | (uint32_t)(2 * NLD);   // vmcnt(2*NLD)
-  auto step = [&](auto b, int t) __attribute__((always_inline)) {
-    constexpr int B = decltype(b)::value;
-    bool async_next = false;
-    if (t + NBUF - 1 < t_hi) async_next = load_tile(std::integral_constant<int, (B + NBUF - 1) % NBUF>{}, t + NBUF - 1);
-    // the tile body works on 64-key sub-tiles (the operand swizzles only
-    // depend on the row modulo 16, so a sub-tile is addressed from its base)
-#pragma unroll
-    for (int sub = 0; sub < BN / 64; ++sub) {
-      const int k0 = t * BN + sub * 64;
-      const uint16_t* Ks = kbuf(b) + sub * 64 * D;
-      const uint16_t* Vs = vbuf(b) + sub * 64 * D;
-      if (wave_active && k0 <= wave_last_lim) {
-        if (k0 + 63 > wave_first_lim)
-          wt.template tile<true>(Ks, Vs, k0, key_lim, hh);
-        else
-          wt.template tile<false>(Ks, Vs, k0, key_lim, hh);
+      if (k0 >= S && k0 + BN <= SW && slot0 + BN <= a.R) {
+        bk = a.ring_k; bv = a.ring_v;
+        rows = a.R; row0 = slot0;
+        n = min(SW - k0, a.R - slot0) / BN;
+      } else {
+        mixed = true;
       }
     }
-    // Tile t + 1 must have landed.  With three buffers the newest tile's
-    // direct loads (issued above, if any) may stay in flight.
-    if (NBUF == 3 && async_next)
-      __builtin_amdgcn_s_waitcnt(kWaitNewestTile);
-    else
-      __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
+    const uint64_t pk = (uint64_t)bk, pv = (uint64_t)bv;
+    run_k = u32x4{(uint32_t)pk, (uint32_t)(pk >> 32) & 0xFFFFu, (uint32_t)(rows * rbytes), 0x00020000u};
+    run_v = u32x4{(uint32_t)pv, (uint32_t)(pv >> 32) & 0xFFFFu, (uint32_t)(rows * rbytes), 0x00020000u};
+    run_so = (uint32_t)row0 * (uint32_t)rbytes;
+    run_left = n;
   };
-  if (t_lo < t_hi) {
-    load_tile(std::integral_constant<int, 0>{}, t_lo);
-    if (NBUF == 3 && t_lo + 1 < t_hi) load_tile(std::integral_constant<int, 1>{}, t_lo + 1);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    for (int t = t_lo; t < t_hi; t += NBUF) {
-      step(std::integral_constant<int, 0>{}, t);
-      if (t + 1 < t_hi) step(std::integral_constant<int, 1>{}, t + 1);
-      if constexpr (NBUF == 3)
-        if (t + 2 < t_hi) step(std::integral_constant<int, 2 % NBUF>{}, t + 2);
+
+  // direct load n (0 .. NLD-1: K, NLD .. 2*NLD-1: V) of the run's tile to the
+  // buffers at byte offset `boff`.  m0 holds a load's LDS address; the
+  // compiler's code in these kernels does not use m0.  The loads have no
+  // result registers.  Wait states that the compiler does not know assembly to
+  // need: one after a write of m0, five after a VALU write of a scalar operand
+  // (the reload of a scalar kept in a VGPR lane is one).
+  const uint32_t my_part = (uint32_t)(wave * NLD * 1024);
+  auto aim = [&](bool v, uint32_t boff) __attribute__((always_inline)) {
+    asm volatile("s_mov_b32 m0, %0" ::"s"(lds0 + my_part + boff + (v ? 0u : kKBase)) : "memory");
+  };
+  auto load_direct = [&](auto idx) __attribute__((always_inline)) {
+    constexpr int i = decltype(idx)::value, n = i % NLD;
+    const uint32_t off = i < NLD ? ld_k[n] : ld_v[n], so = run_so;
+    const u32x4 rs = i < NLD ? run_k : run_v;
+    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %0, %1, %2 offen offset:%3 lds" ::"v"(off), "s"(rs), "s"(so), "n"(n * 1024)
+                 : "memory");
+  };
+
+  // mixed tiles: each lane resolves its key row and the row's tensor; one
+  // direct load per tensor, for that tensor's lanes only (a lane that does not
+  // take part leaves its 16 bytes of LDS alone).  Rows past the chunk's end
+  // are read out of range, as zeros.  The lanes are switched off inside the
+  // assembly: the surrounding code has no divergent branch.
+  auto load_tile_rows = [&](uint32_t boff, int t) __attribute__((always_inline)) {
+    const int k0 = t * BN;
+    auto from = [&](const uint16_t* p, int n, int row, uint32_t unit_off, bool take, uint32_t to)
+        __attribute__((always_inline)) {
+      const uint64_t lanes = __builtin_amdgcn_ballot_w64(take);
+      if (lanes == 0) return;
+      const uint64_t u = (uint64_t)p;
+      const u32x4 rs = u32x4{(uint32_t)u, (uint32_t)(u >> 32) & 0xFFFFu, (uint32_t)(n * rbytes), 0x00020000u};
+      uint64_t all;
+      asm volatile(
+          "s_mov_b64 %0, exec\n\ts_mov_b64 exec, %1\n\ts_mov_b32 m0, %2\n\ts_nop 4\n\t"
+          "buffer_load_dwordx4 %3, %4, 0 offen lds\n\ts_mov_b64 exec, %0"
+          : "=&s"(all)
+          : "s"(lanes), "s"(to), "v"((uint32_t)row * (uint32_t)rbytes + unit_off), "s"(rs)
+          : "memory");
+    };
+    auto rows = [&](const uint16_t* sink, const uint16_t* ring, const uint16_t* chunk, int kk, uint32_t unit_off, uint32_t to)
+        __attribute__((always_inline)) {
+      int slot = a.ws + (kk - S);
+      slot = slot >= a.R ? slot - a.R : slot;
+      from(sink, S, kk, unit_off, kk < S, to);
+      from(ring, a.R, slot, unit_off, kk >= S && kk < SW, to);
+      from(chunk, C, kk - SW, unit_off, kk >= SW, to);
+    };
+#pragma unroll 1
+    for (int n = 0; n < NLD; ++n) {
+      int unit;
+      const int rk = k_row(n, unit);
+      const uint32_t to = lds0 + my_part + boff + n * 1024;
+      rows(a.sink_k, a.ring_k, a.kc, k0 + rk, (uint32_t)(kv * D * 2 + unit * 16), to + kKBase);
+      const int rv = v_row(n, unit);
+      rows(a.sink_v, a.ring_v, a.vc, k0 + rv, (uint32_t)(kv * D * 2 + unit * 16), to);
     }
+  };
+
+  // ---- key loop.  Step t multiplies S of tile t's second half and of tile
+  // t+1's first half, P V of tile t-1's second half and of tile t's first.
+  // The barrier between the two halves certifies tile t+1 and frees V of tile
+  // t-1 (last read in this step's first half), whose buffers take tile
+  // t+AHEAD; its loads go out one by one in the slots of the second half.
+  constexpr int NL = 2 * NLD;                      // direct loads per wave and tile
+  constexpr int LSTEP = (Tile::NSLOT - 2) / (NL + 1);      // slots between two of them
+  static_assert(LSTEP >= 1, "a tile's loads fit a body's slots");
+  // Tile t+1 has landed (the loads of the AHEAD-2 tiles after it may be in
+  // flight), for this wave and every other.  (Not __syncthreads(): that would
+  // wait for all of them, and for the fragment reads.)
+  auto landed = [&]() __attribute__((always_inline)) {
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((AHEAD - 2) * NL) : "memory");
+  };
+  // the rest of a tile's load, after its direct loads
+  auto finish_load = [&](uint32_t boff, int t) __attribute__((always_inline)) {
+    run_so += (uint32_t)(BN * rbytes);
+    if (__builtin_expect(--run_left == 0, 0)) {
+      if (mixed) load_tile_rows(boff, t);
+      start_run(t + 1);
+    }
+  };
+  auto load_whole = [&](uint32_t boff, int t) __attribute__((always_inline)) {
+    aim(false, boff);
+    unrolled<NLD>([&](auto i) __attribute__((always_inline)) { load_direct(i); });
+    aim(true, boff);
+    unrolled<NLD>([&](auto i) __attribute__((always_inline)) {
+      load_direct(std::integral_constant<int, NLD + decltype(i)::value>{});
+    });
+    finish_load(boff, t);
+  };
+
+  f32x16 o[RB][NDB];
+  float m_run[RB], l_run[RB], neg_m[RB];
+  uint32_t k_rd[2], v_rd, v_nx;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) o[rb][db] = f32x16{};
+    m_run[rb] = -INFINITY;
+    neg_m[rb] = INFINITY;
+    l_run[rb] = 0.f;
+  }
+  Tile::start(k_rd, v_nx);
+  k_rd[0] += lds0 + kKBase;                        // tile 0 of the segment: buffer 0
+  k_rd[1] += lds0 + kKBase;
+  v_nx += lds0;
+  v_rd = v_nx + (NB - 1) * TBY;                    // the tile before it: the last buffer
+  if (t_lo < t_hi) {
+    start_run(t_lo);
+#pragma unroll 1
+    for (int i = 0; i < AHEAD; ++i) load_whole(i * TBY, t_lo + i);
+    // the pipeline's first P V multiplies zero probabilities with the last 16
+    // rows of the last V buffer: any bits there must be finite
+    if (tid < 16 * UPR)
+      *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(lds0 + (NB - 1) * TBY + 48 * RBY + tid * 16) =
+          u32x4{0, 0, 0, 0};
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((AHEAD - 1) * NL) : "memory");   // tile t_lo
+    uint32_t boff = 0;                             // buffer offset of tile t
+    constexpr uint32_t kWrap = NB * TBY - 1;
+    static_assert((NB & (NB - 1)) == 0, "buffer offsets wrap by a mask");
+    if (wave_active) {
+      bf16x8 vf[NDB] = {};
+      Tile wt{qf, k_rd, v_rd, v_nx, o, m_run, l_run, neg_m, vf, a.scale_log2};
+      f32x16 s0[RB], s1[RB];
+      bf16x8 p0[RB][2] = {}, p1[RB][2] = {};
+      wt.first_logits(s0);
+      const int t_mask = wave_first_lim < 63 ? 0 : (wave_first_lim - 63) / BN + 1;   // tiles from here on may need the mask
+      if (t_lo >= t_mask) Tile::mask(t_lo * BN, key_lim, hh, s0);
+      wt.first_max(s0);
+      for (int t = t_lo; t < t_hi; ++t) {
+        if (__builtin_expect(t >= t_mask, 0)) Tile::mask(t * BN, key_lim, hh, s0);
+        uint32_t next = 0;                         // of tile t+1
+        wt.template half<32, 48, 0>(s0, s1, p1, p0, [&](auto slot) __attribute__((always_inline)) {
+          constexpr int s = decltype(slot)::value;
+          if constexpr (s == Tile::NQK + Tile::NPV) {
+            next = (boff + TBY) & kWrap;
+            k_rd[0] += next - boff;                // K of tile t+1
+            k_rd[1] += next - boff;
+            v_rd = v_nx;                           // V of tile t
+          }
+        });
+        landed();
+        if (__builtin_expect(t >= t_mask, 0)) Tile::mask(t * BN + 32, key_lim, hh, s1);
+        const uint32_t fill = (boff + AHEAD * TBY) & kWrap;
+        wt.template half<0, 16, 32>(s1, s0, p0, p1, [&](auto slot) __attribute__((always_inline)) {
+          constexpr int s = decltype(slot)::value, i = s / LSTEP - 1;
+          if constexpr (s == 1) aim(false, fill);
+          if constexpr (s == NLD * LSTEP + 1) aim(true, fill);
+          if constexpr (s % LSTEP == 0 && i >= 0 && i < NL) load_direct(std::integral_constant<int, i>{});
+        });
+        v_nx += next - boff;                       // V of tile t+1
+        boff = next;
+        finish_load(fill, t + AHEAD);
+      }
+      wt.template last_values<48>(p1);
+    } else {
+      for (int t = t_lo; t < t_hi; ++t) {
+        landed();
+        load_whole((boff + AHEAD * TBY) & kWrap, t + AHEAD);
+        boff = (boff + TBY) & kWrap;
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the empty loads past the last tile
   }
 
   if (!wave_active) return;
-  constexpr int NDB = WaveTile<D>::NDB;
-  const int row = tok;
-  float inv, lse2;
-  wt.finish(inv, lse2);
-  if (wrow0 + l32 >= NR) return;
-  if (!partial) {
-    if (a.out_f32) {
-      float* op = (float*)a.out + ((int64_t)row * a.Hq + h) * D + hh * 4;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    // row totals over the two lanes of a row
+    const float l_tot = pair_sum(l_run[rb]);
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;                              // 0 for an empty row
+    const float lse2 = l_tot > 0.f ? m_run[rb] + __log2f(l_tot) : -INFINITY;
+    if (wrow0 + rb * 32 + l32 >= NR) continue;
+    const int row = tok[rb], hd = h[rb];
+    if (partial || a.out_f32) {
+      float* op = partial ? a.ws_o + (((int64_t)part * a.Hq + hd) * C + row) * D
+                          : (float*)a.out + ((int64_t)row * a.Hq + hd) * D;
+      op += hh * 4;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
-          const f32x16& x = o[db];
+          const f32x16& x = o[rb][db];
           *(f32x4*)(op + db * 32 + q4 * 8) =
               f32x4{x[q4 * 4] * inv, x[q4 * 4 + 1] * inv, x[q4 * 4 + 2] * inv, x[q4 * 4 + 3] * inv};
         }
     } else {
-      __bf16* op = (__bf16*)a.out + ((int64_t)row * a.Hq + h) * D + hh * 4;
+      __bf16* op = (__bf16*)a.out + ((int64_t)row * a.Hq + hd) * D + hh * 4;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
-          const f32x16& x = o[db];
+          const f32x16& x = o[rb][db];
           *(bf16x4*)(op + db * 32 + q4 * 8) =
               bf16x4{(__bf16)(x[q4 * 4] * inv), (__bf16)(x[q4 * 4 + 1] * inv), (__bf16)(x[q4 * 4 + 2] * inv),
                      (__bf16)(x[q4 * 4 + 3] * inv)};
         }
     }
-    if (a.lse && hh == 0) a.lse[(int64_t)h * C + row] = lse2 * kLn2;
-  } else {
-    float* op = a.ws_o + (((int64_t)part * a.Hq + h) * C + row) * D + hh * 4;
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const f32x16& x = o[db];
-        *(f32x4*)(op + db * 32 + q4 * 8) =
-            f32x4{x[q4 * 4] * inv, x[q4 * 4 + 1] * inv, x[q4 * 4 + 2] * inv, x[q4 * 4 + 3] * inv};
-      }
-    if (hh == 0) {
-      a.ws_lse[((int64_t)part * a.Hq + h) * C + row] = lse2;
+    if (hh != 0) continue;
+    if (!partial) {
+      if (a.lse) a.lse[(int64_t)hd * C + row] = lse2 * kLn2;
+    } else {
+      a.ws_lse[((int64_t)part * a.Hq + hd) * C + row] = lse2;
       // a row tile that ends in this segment uses no later parts
       if (t_hi == n_tiles)
-        for (int p2 = part + 1; p2 < n_parts; ++p2) a.ws_lse[((int64_t)p2 * a.Hq + h) * C + row] = -INFINITY;
+        for (int p2 = part + 1; p2 < n_parts; ++p2) a.ws_lse[((int64_t)p2 * a.Hq + hd) * C + row] = -INFINITY;
     }
   }
   };   // segment

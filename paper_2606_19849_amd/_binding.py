@@ -1,4 +1,8 @@
-"""ctypes binding of libvico (include/vico.h): argument marshalling only.
+"""Binding of libvico (include/vico.h): argument marshalling only.
+
+Calls with plain arguments go through _vico_call (csrc/py_call.cpp), which
+checks and passes them in C++; it answers None for anything else, and the
+ctypes path here then accepts or rejects the call.
 
 Every computation runs in the HIP kernels of libvico.so.  torch supplies the
 device buffers and the stream; it is imported before the library is loaded
@@ -8,6 +12,7 @@ the calls raise -- there is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 import re
 
@@ -54,7 +59,9 @@ _SIGNATURES = {
     "vico_last_hip_error": (_i32, []),
 }
 
+CALL_PATH = os.path.join(PKG, "_vico_call.so")
 _lib = None
+_calls = None
 
 
 class VicoError(RuntimeError):
@@ -78,6 +85,25 @@ def load_library():
             fn.restype, fn.argtypes = res, args
         _lib = lib
     return _lib
+
+
+def _fast():
+    """The C++ calls; raise ImportError if they have not been built."""
+    global _calls
+    if _calls is None:
+        load_library()
+        if not os.path.exists(CALL_PATH):
+            raise ImportError(f"{CALL_PATH} is missing; build it with `python -m paper_2606_19849_amd.build`")
+        spec = importlib.util.spec_from_file_location("_vico_call", CALL_PATH)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        _calls = mod
+    return _calls
+
+
+def _handle(stream):
+    """A stream argument as _vico_call takes it: None (the current stream) or the handle."""
+    return None if stream is None else getattr(stream, "cuda_stream", stream)
 
 
 def header_functions():
@@ -114,6 +140,9 @@ def _dev_bf16(name, t, ndim=3):
 
 def vico_kv_append(k_chunk, v_chunk, ring_k, ring_v, hist_len: int, stream=None) -> None:
     """ring[(hist_len + j) % R] <- chunk[j] for K and V (vico_kv_append)."""
+    st = (_calls or _fast()).kv_append(k_chunk, v_chunk, ring_k, ring_v, hist_len, _handle(stream))
+    if st is not None:
+        return _check(st, "vico_kv_append")
     for n, t in (("k_chunk", k_chunk), ("v_chunk", v_chunk), ("ring_k", ring_k), ("ring_v", ring_v)):
         _dev_bf16(n, t)
     C, Hkv, D = k_chunk.shape
@@ -155,6 +184,10 @@ def vico_chunk_prefill_attn(q, k_chunk, v_chunk, sink_k, sink_v, ring_k, ring_v,
                             out, lse=None, workspace=None, num_splits: int = 0, softmax_scale: float = 0.0,
                             stream=None, flags: int = 0) -> None:
     """Bounded chunk-prefill attention (vico_chunk_prefill_attn_ex); writes `out` (and `lse`)."""
+    st = (_calls or _fast()).prefill(q, k_chunk, v_chunk, sink_k, sink_v, ring_k, ring_v, hist_len, window, out, lse,
+                                     workspace, num_splits, softmax_scale, _handle(stream), flags)
+    if st is not None:
+        return _check(st, "vico_chunk_prefill_attn_ex")
     for n, t in (("q", q), ("k_chunk", k_chunk), ("v_chunk", v_chunk), ("sink_k", sink_k),
                  ("sink_v", sink_v), ("ring_k", ring_k), ("ring_v", ring_v)):
         _dev_bf16(n, t)
@@ -186,6 +219,9 @@ def _dev_tensor(name, t, dtype, ndim):
 
 def vico_token_mean(x, out, stream=None) -> None:
     """out[c] = mean over tokens of x[t][c] (vico_token_mean); x bf16 [L, dm], out fp32 [dm]."""
+    st = (_calls or _fast()).token_mean(x, out, _handle(stream))
+    if st is not None:
+        return _check(st, "vico_token_mean")
     _dev_tensor("x", x, torch.bfloat16, 2)
     _dev_tensor("out", out, torch.float32, 1)
     L, dm = x.shape
@@ -196,6 +232,9 @@ def vico_token_mean(x, out, stream=None) -> None:
 
 def vico_chunk_scores(query_feat, chunk_feat, scores, stream=None) -> None:
     """Cosine of the query feature with every chunk feature (vico_chunk_scores)."""
+    st = (_calls or _fast()).chunk_scores(query_feat, chunk_feat, scores, _handle(stream))
+    if st is not None:
+        return _check(st, "vico_chunk_scores")
     _dev_tensor("query_feat", query_feat, torch.float32, 1)
     _dev_tensor("chunk_feat", chunk_feat, torch.float32, 2)
     _dev_tensor("scores", scores, torch.float32, 1)
@@ -209,6 +248,10 @@ def vico_chunk_scores(query_feat, chunk_feat, scores, stream=None) -> None:
 def vico_topk_chunks(scores, top_k: int, out_chunks, out_scores, out_count, min_score: float = float("-inf"),
                      chunk_start=None, chunk_len=None, seg_start=None, seg_len=None, stream=None) -> None:
     """Top-k chunks by score with score >= min_score, in stream order (vico_topk_chunks)."""
+    st = (_calls or _fast()).topk_chunks(scores, top_k, out_chunks, out_scores, out_count, min_score, chunk_start,
+                                         chunk_len, seg_start, seg_len, _handle(stream))
+    if st is not None:
+        return _check(st, "vico_topk_chunks")
     _dev_tensor("scores", scores, torch.float32, 1)
     _dev_tensor("out_chunks", out_chunks, torch.int32, 1)
     _dev_tensor("out_scores", out_scores, torch.float32, 1)
@@ -272,6 +315,10 @@ def vico_gather_attn(q, tail_k, tail_v, sink_k, sink_v, store_k, store_v, seg_st
                      workspace=None, keys_hint: int = 0, num_splits: int = 0, softmax_scale: float = 0.0,
                      stream=None) -> None:
     """Short-query attention over sink ++ store segments ++ causal tail (vico_gather_attn)."""
+    st = (_calls or _fast()).gather(q, tail_k, tail_v, sink_k, sink_v, store_k, store_v, seg_start, seg_len, out, lse,
+                                    keys_hint, num_splits, softmax_scale, _handle(stream), workspace)
+    if st is not None:
+        return _check(st, "vico_gather_attn")
     args = _gather_args(q, tail_k, tail_v, sink_k, sink_v, store_k, store_v, seg_start, seg_len, out, lse,
                         keys_hint, softmax_scale)
     wb = 0 if workspace is None else workspace.numel() * workspace.element_size()
@@ -284,6 +331,10 @@ def vico_gather_attn_noalloc(q, tail_k, tail_v, sink_k, sink_v, store_k, store_v
                              stream=None) -> None:
     """vico_gather_attn with the library's fixed device array as workspace
     (vico_gather_attn_noalloc); allocates nothing, here or in the library."""
+    st = (_calls or _fast()).gather_noalloc(q, tail_k, tail_v, sink_k, sink_v, store_k, store_v, seg_start, seg_len, out,
+                                            lse, keys_hint, num_splits, softmax_scale, _handle(stream))
+    if st is not None:
+        return _check(st, "vico_gather_attn_noalloc")
     args = _gather_args(q, tail_k, tail_v, sink_k, sink_v, store_k, store_v, seg_start, seg_len, out, lse,
                         keys_hint, softmax_scale)
     st = load_library().vico_gather_attn_noalloc(*args, int(num_splits), _stream(stream))
@@ -304,6 +355,10 @@ def vico_temporal_drop(frames, tau: float, keep, out_index, out_count, sim=None,
     """Chunk-level temporal token dropping (vico_temporal_drop); frames bf16 [B, C, n_f, dm].
     With a workspace of vico_temporal_drop_workspace_bytes(B, C, n_f, dm) bytes
     the call takes the single-pass schedule where it applies."""
+    st = (_calls or _fast()).temporal_drop(frames, tau, keep, out_index, out_count, sim, out_tokens, prev_frame, workspace,
+                                           _handle(stream))
+    if st is not None:
+        return _check(st, "vico_temporal_drop")
     _dev_tensor("frames", frames, torch.bfloat16, 4)
     B, C, n_f, dm = frames.shape
     _dev_tensor("keep", keep, torch.uint8, 2)

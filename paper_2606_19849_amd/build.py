@@ -1,5 +1,6 @@
 """Compile libvico.so (HIP kernels + C ABI) and the measurement helper
-libvico_bench.so for gfx950, in-tree.
+libvico_bench.so for gfx950, and the binding's C++ calls (_vico_call.so),
+in-tree.
 
 Usage: python -m paper_2606_19849_amd.build   (or build() from Python)
 """
@@ -18,6 +19,9 @@ SOURCES = ["attn_fwd.hip", "attn_merge.hip", "attn_gather.hip", "attn_rows.hip",
 BENCH_LIB = os.path.join(PKG, "libvico_bench.so")
 BENCH_SOURCES = ["mfma_peak.hip"]
 
+CALL_LIB = os.path.join(PKG, "_vico_call.so")
+CALL_SOURCE = "py_call.cpp"
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -35,10 +39,32 @@ FLAGS = [
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:
-    """Compile libvico.so and libvico_bench.so; return the path of libvico.so."""
+    """Compile libvico.so, libvico_bench.so and _vico_call.so; return the path of libvico.so."""
     _compile(SOURCES, LIB, verbose, extra_flags)
     _compile(BENCH_SOURCES, BENCH_LIB, verbose, extra_flags)
+    _compile_calls(verbose)
     return LIB
+
+
+def _compile_calls(verbose) -> None:
+    """The binding's C++ calls: host code against torch's headers and libvico.so."""
+    import sysconfig
+
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    tmp = CALL_LIB + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INCLUDE, "-I", inc,
+           "-I", os.path.join(inc, "torch", "csrc", "api", "include"), "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), os.path.join(CSRC, CALL_SOURCE),
+           "-o", tmp, "-L", PKG, "-l:libvico.so", "-L", os.path.join(os.path.dirname(torch.__file__), "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed ({res.returncode}):\n{res.stderr}")
+    os.replace(tmp, CALL_LIB)
 
 
 def _compile(sources, lib, verbose, extra_flags) -> None:

@@ -12,6 +12,8 @@
 // workspace.  Every reduction runs in a fixed order, so results repeat
 // bit for bit.
 
+#include <type_traits>
+
 #include "attn_common.h"
 
 namespace vico {
@@ -114,42 +116,26 @@ struct TopkArgs {
   int32_t* out_count;
 };
 
-// Exclusive block-wide prefix sum of v (NT threads); *total gets the sum.
-// `buf` holds one slot per wave; the caller separates successive calls with
-// a barrier (done at the end here).
-template <int NT>
-__device__ __forceinline__ int block_scan(int v, int* buf, int* total) {
-  constexpr int NW = NT / 64;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += y;
-  }
-  if (lane == 63) buf[wave] = incl;
-  __syncthreads();
-  int base = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    const int t = buf[w];
-    base += w < wave ? t : 0;
-    tot += t;
-  }
-  __syncthreads();
-  *total = tot;
-  return base + incl - v;
-}
-
-// NT threads: 256 for up to 256 scores (fewer waves to synchronise at each
-// of the select's barriers), else 1024.
-template <int NT>
+// Radix select of the k-th largest key, 8 bits at a time from the top, then
+// one numbering of the selected scores in index order.  One work-group, bound
+// by the latency of its barriers and LDS round trips, so it makes few: every
+// digit has its own histogram (cleared together), every wave finds the digit
+// for itself from the histogram (no second barrier), and the scores kept in
+// registers are numbered in one step from their ballots.  6 barriers (3 where
+// all candidates are taken); with three barriers per digit and four per
+// numbering step it took 6.5 us at 256 scores and 9.4 at 1800, now 4.9 and 6.8
+// (traced).
+//
+// NT threads: 256 for up to 256 scores (fewer waves to wait for), else 1024.
+// The first NR * NT keys stay in registers; further ones are read again.  2
+// and 8 keys per thread are separate kernels: at 1800 scores the walk over 8
+// mostly empty registers took 10.0 us against 6.8.
+template <int NT, int NR>
 __global__ __launch_bounds__(NT) void topk_kernel(TopkArgs a) {
-  static_assert(NT >= 256, "one thread per histogram bin");
-  constexpr int NR = kTopkRegKeys;
-  __shared__ int hist[256];
-  __shared__ int scan_buf[NT / 64];
-  __shared__ int sh_bin, sh_remaining;
+  constexpr int NW = NT / 64;
+  static_assert(NR * NW <= 128, "a wave scans the per-wave counts of all register keys, two per lane");
+  __shared__ int hist[4][256];
+  __shared__ int cnt_gt[128], cnt_eq[128];           // selected / equal keys per (register, wave)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // key of score i, 0 for "not a candidate" (0 is the key of a NaN pattern,
   // which is never a candidate)
@@ -157,99 +143,122 @@ __global__ __launch_bounds__(NT) void topk_kernel(TopkArgs a) {
     const float s = a.scores[i];
     return (!isnan(s) && s >= a.min_score) ? order_key(s) : 0u;
   };
-  // the first NR * NT keys stay in registers; the rest are re-read
   uint32_t kr[NR];
 #pragma unroll
   for (int j = 0; j < NR; ++j) {
     const int i = tid + j * NT;
     kr[j] = i < a.N ? key_of(i) : 0u;
   }
-  auto for_each_key = [&](auto&& fn) __attribute__((always_inline)) {
-#pragma unroll
-    for (int j = 0; j < NR; ++j) fn(kr[j]);
-    for (int i = tid + NR * NT; i < a.N; i += NT) fn(key_of(i));
-  };
+  for (int i = tid; i < 4 * 256; i += NT) (&hist[0][0])[i] = 0;
+  __syncthreads();
 
-  int cnt = 0;
-  for_each_key([&](uint32_t k) __attribute__((always_inline)) { cnt += k != 0u; });
-  int n_cand;
-  block_scan<NT>(cnt, scan_buf, &n_cand);
-  const bool take_all = n_cand <= a.k;
-
-  // radix select of the k-th largest key, 8 bits at a time from the top
+  // digits of the k-th largest key.  Lane l of every wave holds bins 255-4l ..
+  // 252-4l and finds where the count from the top first reaches `remaining`.
   uint32_t prefix = 0, mask = 0;
   int remaining = a.k;
-  if (!take_all) {
-    for (int shift = 24; shift >= 0; shift -= 8) {
-      if (tid < 256) hist[tid] = 0;
-      __syncthreads();
-      for_each_key([&](uint32_t k) __attribute__((always_inline)) {
-        if (k != 0u && (k & mask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1);
-      });
-      __syncthreads();
-      if (wave == 0) {
-        // lane l holds bins 255-4l .. 252-4l; find the bin where the count of
-        // keys from the top first reaches `remaining`
-        int c[4], tot = 0;
+  bool take_all = false;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { c[e] = hist[255 - 4 * lane - e]; tot += c[e]; }
-        int incl = tot;
+  for (int d = 0; d < 4; ++d) {
+    const int shift = 24 - 8 * d;
+    auto count = [&](uint32_t k) __attribute__((always_inline)) {
+      if (k != 0u && (k & mask) == prefix) atomicAdd(&hist[d][(k >> shift) & 255u], 1);
+    };
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const int y = __shfl_up(incl, o, 64);
-          if (lane >= o) incl += y;
-        }
-        int cum = incl - tot;
-        if (cum < remaining && incl >= remaining) {
-          int e_hit = 3, cum_hit = cum;
-          bool found = false;
+    for (int j = 0; j < NR; ++j) count(kr[j]);
+    for (int i = tid + NR * NT; i < a.N; i += NT) count(key_of(i));
+    __syncthreads();
+    int c[4], tot = 0;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (!found && cum + c[e] >= remaining) { found = true; e_hit = e; cum_hit = cum; }
-            cum += c[e];
-          }
-          sh_bin = 255 - 4 * lane - e_hit;
-          sh_remaining = remaining - cum_hit;
-        }
-      }
-      __syncthreads();
-      prefix |= (uint32_t)sh_bin << shift;
-      mask |= 255u << shift;
-      remaining = sh_remaining;
+    for (int e = 0; e < 4; ++e) {
+      c[e] = hist[d][255 - 4 * lane - e];
+      tot += c[e];
     }
+    int incl = tot;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(incl, o, 64);
+      incl += lane >= o ? y : 0;
+    }
+    if (d == 0 && __builtin_amdgcn_readlane(incl, 63) <= a.k) {      // no more candidates than asked for
+      take_all = true;
+      break;
+    }
+    const int before = incl - tot;
+    const int hit = __builtin_ctzll(__builtin_amdgcn_ballot_w64(before < remaining && incl >= remaining));
+    int cum = __builtin_amdgcn_readlane(before, hit), bin = 255 - 4 * hit;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {                    // which of the lane's four bins (wave-uniform)
+      const int n = __builtin_amdgcn_readlane(c[e], hit);
+      const bool past = bin == 255 - 4 * hit - e && cum + n < remaining;
+      cum += past ? n : 0;
+      bin -= past ? 1 : 0;
+    }
+    remaining -= cum;
+    prefix |= (uint32_t)bin << shift;
+    mask |= 255u << shift;
   }
   // prefix = key of the k-th best; keys above it are all taken, and
-  // `remaining` of those equal to it, earliest first
-
-  int taken = 0, eq_seen = 0;
-  auto emit = [&](int i, uint32_t key) __attribute__((always_inline)) {
-    const bool cand = key != 0u;
-    const bool gt = cand && (take_all || key > prefix);
-    const bool eq = cand && !take_all && key == prefix;
-    int eq_tot;
-    const int eq_rank = eq_seen + block_scan<NT>(eq ? 1 : 0, scan_buf, &eq_tot);
-    const bool sel = gt || (eq && eq_rank < remaining);
-    int sel_tot;
-    const int pos = taken + block_scan<NT>(sel ? 1 : 0, scan_buf, &sel_tot);
-    if (sel) {
-      a.out_chunks[pos] = i;
-      a.out_scores[pos] = a.scores[i];
-      if (a.seg_start) {
-        a.seg_start[pos] = a.chunk_start[i];
-        a.seg_len[pos] = a.chunk_len[i];
+  // `remaining` of those equal to it, earliest first.  A selected score's place
+  // is the number of taken ones before it.
+  auto is_gt = [&](uint32_t k) __attribute__((always_inline)) { return k != 0u && (take_all || k > prefix); };
+  auto is_eq = [&](uint32_t k) __attribute__((always_inline)) { return k != 0u && !take_all && k == prefix; };
+  auto put = [&](int pos, int i) __attribute__((always_inline)) {
+    a.out_chunks[pos] = i;
+    a.out_scores[pos] = a.scores[i];
+    if (a.seg_start) {
+      a.seg_start[pos] = a.chunk_start[i];
+      a.seg_len[pos] = a.chunk_len[i];
+    }
+  };
+  const uint64_t below = (1ull << lane) - 1;
+  // numbers NG groups of NT consecutive scores; key(j) is this thread's key in group j, i0 the first score
+  int gt_seen = 0, eq_seen = 0;
+  auto number = [&](auto groups, auto&& key, int i0) __attribute__((always_inline)) {
+    constexpr int NG = decltype(groups)::value;
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+      const uint64_t g = __builtin_amdgcn_ballot_w64(is_gt(key(j))), q = __builtin_amdgcn_ballot_w64(is_eq(key(j)));
+      if (lane == 0) {
+        cnt_gt[j * NW + wave] = __builtin_popcountll(g);
+        cnt_eq[j * NW + wave] = __builtin_popcountll(q);
       }
     }
-    taken += sel_tot;
-    eq_seen += eq_tot;
-  };
-  // in index order, one block-wide step of NT scores at a time
+    __syncthreads();
+    // exclusive counts before each (group, wave): two entries per lane, every wave for itself
+    constexpr int NE = NG * NW;
+    const int e0 = 2 * lane < NE ? cnt_gt[2 * lane] : 0, e1 = 2 * lane + 1 < NE ? cnt_gt[2 * lane + 1] : 0;
+    const int f0 = 2 * lane < NE ? cnt_eq[2 * lane] : 0, f1 = 2 * lane + 1 < NE ? cnt_eq[2 * lane + 1] : 0;
+    int ig = e0 + e1, iq = f0 + f1;
 #pragma unroll
-  for (int j = 0; j < NR; ++j)
-    if (j * NT < a.N) emit(tid + j * NT, kr[j]);
+    for (int o = 1; o < 64; o <<= 1) {
+      const int yg = __shfl_up(ig, o, 64), yq = __shfl_up(iq, o, 64);
+      ig += lane >= o ? yg : 0;
+      iq += lane >= o ? yq : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+      const int w = __builtin_amdgcn_readfirstlane(j * NW + wave), src = w >> 1;
+      const int gt_w = __builtin_amdgcn_readlane(ig, src) - __builtin_amdgcn_readlane(e1, src) -
+                       ((w & 1) ? 0 : __builtin_amdgcn_readlane(e0, src));
+      const int eq_w = __builtin_amdgcn_readlane(iq, src) - __builtin_amdgcn_readlane(f1, src) -
+                       ((w & 1) ? 0 : __builtin_amdgcn_readlane(f0, src));
+      const bool gt = is_gt(key(j)), eq = is_eq(key(j));
+      const uint64_t g = __builtin_amdgcn_ballot_w64(gt), q = __builtin_amdgcn_ballot_w64(eq);
+      const int gt_before = gt_seen + gt_w + __builtin_popcountll(g & below);
+      const int eq_before = eq_seen + eq_w + __builtin_popcountll(q & below);
+      if (gt || (eq && eq_before < remaining)) put(gt_before + min(eq_before, remaining), i0 + j * NT + tid);
+    }
+    gt_seen += __builtin_amdgcn_readlane(ig, 63);
+    eq_seen += __builtin_amdgcn_readlane(iq, 63);
+  };
+  number(std::integral_constant<int, NR>{}, [&](int j) __attribute__((always_inline)) { return kr[j]; }, 0);
   for (int i0 = NR * NT; i0 < a.N; i0 += NT) {
     const int i = i0 + tid;
-    emit(i, i < a.N ? key_of(i) : 0u);
+    const uint32_t k = i < a.N ? key_of(i) : 0u;
+    __syncthreads();                                 // the counts of the step before have been read
+    number(std::integral_constant<int, 1>{}, [&](int) __attribute__((always_inline)) { return k; }, i0);
   }
+  const int taken = gt_seen + min(eq_seen, take_all ? 0 : remaining);
   for (int j = taken + tid; j < a.k; j += NT) {
     a.out_chunks[j] = -1;
     a.out_scores[j] = -INFINITY;
@@ -280,10 +289,13 @@ hipError_t launch_topk(const float* scores, int N, int k, float min_score, const
                        const int32_t* chunk_len, int32_t* out_chunks, float* out_scores, int64_t* seg_start,
                        int32_t* seg_len, int32_t* out_count, hipStream_t stream) {
   TopkArgs a{scores, N, k, min_score, chunk_start, chunk_len, out_chunks, out_scores, seg_start, seg_len, out_count};
-  if (N <= 256)   // one score per thread (measured: 7.8 vs 9.3 us at N = 256; slower from N = 1000)
-    hipLaunchKernelGGL(topk_kernel<256>, dim3(1), dim3(256), 0, stream, a);
+  // the smallest form whose registers hold all scores
+  if (N <= 256)
+    hipLaunchKernelGGL((topk_kernel<256, 1>), dim3(1), dim3(256), 0, stream, a);
+  else if (N <= 2 * kTopkThreads)
+    hipLaunchKernelGGL((topk_kernel<kTopkThreads, 2>), dim3(1), dim3(kTopkThreads), 0, stream, a);
   else
-    hipLaunchKernelGGL(topk_kernel<kTopkThreads>, dim3(1), dim3(kTopkThreads), 0, stream, a);
+    hipLaunchKernelGGL((topk_kernel<kTopkThreads, kTopkRegKeys>), dim3(1), dim3(kTopkThreads), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -76,6 +76,14 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int g
   __shared__ __attribute__((aligned(16))) uint8_t lds[2 * NB * TBY];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void*)lds;
 
+  // ---- the append's share: slots that no work-group of this launch reads
+  const int n_work = gridDim.x - a.app_blocks;
+  if ((int)blockIdx.x >= n_work) {
+    const AppendArgs ap{a.kc, a.vc, a.app_rk, a.app_rv, a.C, a.R, a.app_p0, a.Hkv * a.D};
+    append_units(ap, (int64_t)(blockIdx.x - n_work) * kThreads + threadIdx.x, (int64_t)a.app_blocks * kThreads);
+    return;
+  }
+
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -409,7 +417,7 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int g
   };   // segment
 
   // ---- schedule
-  const int L = xcd_remap(blockIdx.x, gridDim.x);
+  const int L = xcd_remap(blockIdx.x, n_work);
   if (!a.balanced) {
     // one row tile (one key range of it when split) per work-group
     const int qh = L % gq;
@@ -427,7 +435,7 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int g
     // kv, row tile (longest first), head group, are cut into gridDim.x equal
     // ranges.  A row tile cut between work-groups is finished by the merge
     // kernel; part = index of the work-group among those covering it.
-    const int64_t G = gridDim.x, T = a.total_tiles;
+    const int64_t G = n_work, T = a.total_tiles;
     int64_t pos = (int64_t)L * T / G;
     const int64_t end = (int64_t)(L + 1) * T / G;
     bool first = true;
@@ -478,7 +486,7 @@ hipError_t launch_attention(const AttnArgs& a, int grid, hipStream_t stream) {
   if (a.pack < 1 || g % a.pack != 0) return hipErrorInvalidValue;
   const int gq = g / a.pack;
   const int n_rt = (int)(((int64_t)a.C * a.pack + kBlockM - 1) / kBlockM);
-  const dim3 gr(grid), bl(kThreads);
+  const dim3 gr(grid + a.app_blocks), bl(kThreads);
   if (a.pack == 1) {
     if (a.D == 128) hipLaunchKernelGGL(attn_fwd_kernel<128>, gr, bl, 0, stream, a, n_rt, gq);
     else hipLaunchKernelGGL(attn_fwd_kernel<64>, gr, bl, 0, stream, a, n_rt, gq);
@@ -489,7 +497,7 @@ hipError_t launch_attention(const AttnArgs& a, int grid, hipStream_t stream) {
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   if (a.splits > 1) return launch_merge(a, stream);   // appends too, when asked
-  if (!a.app_rk) return err;
+  if (!a.app_rk || a.app_blocks > 0) return err;
   const AppendArgs ap{a.kc, a.vc, a.app_rk, a.app_rv, a.C, a.R, a.app_p0, a.Hkv * a.D};
   return launch_append(ap, stream);
 }

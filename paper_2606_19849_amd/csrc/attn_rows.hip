@@ -10,10 +10,12 @@
 // to the last key's arrival and by how many bytes are in flight; staging tiles
 // in LDS for one or two computing waves serialises a work-group behind its
 // barriers.  Here every wave works alone: it takes 32-key blocks of its
-// work-group's key range in turn, loads them into registers (the next
-// block while it computes one), and keeps its own running softmax state.
+// work-group's key range in turn, loads them into registers and keeps its own
+// running softmax state.
 // There is no barrier before the end, where the waves' states are merged
-// through LDS.
+// through LDS.  8 waves: 12 measured the same on the 20.5k-key decode step
+// (16.1 us a layer with its merge; staged through LDS 22.6), 16 at 128
+// registers each spill (24.4).
 //   * v_mfma_f32_16x16x32_bf16.  S^T = K Q^T: the A operand wants 8
 //     consecutive dims of one key row per lane, which is a 16-byte load.  The
 //     32 keys are two 16-key products whose row order is chosen so that lane
@@ -33,7 +35,7 @@
 namespace vico {
 namespace {
 
-template <int D, int NRB, int NW, bool PF>   // PF: the next block loads while one is computed
+template <int D, int NRB, int NW>
 __global__ __launch_bounds__(NW * 64, 1) void attn_rows_kernel(RowsArgs a) {
   constexpr int NKS = D / 32;              // k-steps of Q K^T
   constexpr int VE = D / 16;               // dims per lane of a V row
@@ -46,6 +48,13 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_rows_kernel(RowsArgs a) {
   __shared__ __attribute__((aligned(16))) float o_s[NW][RT][OS];
   __shared__ float m_s[NW][RT], l_s[NW][RT];
 
+  // ---- the append's share: slots that no work-group of this launch reads
+  const int n_work = gridDim.x - a.app_blocks;
+  if ((int)blockIdx.x >= n_work) {
+    append_units(a.app, (int64_t)(blockIdx.x - n_work) * blockDim.x + threadIdx.x, (int64_t)a.app_blocks * blockDim.x);
+    return;
+  }
+
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, j = lane >> 4;
@@ -53,7 +62,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_rows_kernel(RowsArgs a) {
   const int NR = g * a.Lq;
 
   // ---- work item: row tiles of one key range side by side (they share its K/V in an XCD's L2)
-  const int L = xcd_remap(blockIdx.x, gridDim.x);
+  const int L = xcd_remap(blockIdx.x, n_work);
   const int rt = L % a.n_rt;
   const int part = (L / a.n_rt) % a.parts;
   const int kv = L / (a.n_rt * a.parts);
@@ -258,28 +267,14 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_rows_kernel(RowsArgs a) {
     }
   };
 
-  // ---- the wave's blocks, the next one loading while one is computed
-  {
-    u32x4 k0[2][NKS], k1[2][NKS];
-    vrow_t v0[8], v1[8];
-    int b = b_lo + wave;
-    if constexpr (PF) {
-      if (b < b_hi) load_block(b, k0, v0);
-      while (b < b_hi) {
-        if (b + NW < b_hi) load_block(b + NW, k1, v1);
-        compute_block(b, k0, v0);
-        b += NW;
-        if (b >= b_hi) break;
-        if (b + NW < b_hi) load_block(b + NW, k0, v0);
-        compute_block(b, k1, v1);
-        b += NW;
-      }
-    } else {
-      for (; b < b_hi; b += NW) {
-        load_block(b, k0, v0);
-        compute_block(b, k0, v0);
-      }
-    }
+  // ---- the wave's blocks.  (Loading the next block while one is computed was
+  // measured 1-7 % slower: the other waves' loads fill the gap, and the
+  // second set of registers only lengthens the start.)
+  for (int b = b_lo + wave; b < b_hi; b += NW) {
+    u32x4 kr[2][NKS];
+    vrow_t vr[8];
+    load_block(b, kr, vr);
+    compute_block(b, kr, vr);
   }
 
   // ---- merge of the waves: O^T lane (n, j) holds row n, dims VE*(4j+i) + e
@@ -334,10 +329,10 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_rows_kernel(RowsArgs a) {
 
 template <int D>
 hipError_t launch(const RowsArgs& a, hipStream_t stream) {
-  const dim3 grid(a.n_rt * a.parts * a.Hkv);
+  const dim3 grid(a.n_rt * a.parts * a.Hkv + a.app_blocks);
   switch (a.row_blocks) {
-    case 1: hipLaunchKernelGGL((attn_rows_kernel<D, 1, 8, true>), grid, dim3(512), 0, stream, a); break;
-    case 2: hipLaunchKernelGGL((attn_rows_kernel<D, 2, 8, D == 64>), grid, dim3(512), 0, stream, a); break;
+    case 1: hipLaunchKernelGGL((attn_rows_kernel<D, 1, 8>), grid, dim3(512), 0, stream, a); break;
+    case 2: hipLaunchKernelGGL((attn_rows_kernel<D, 2, 8>), grid, dim3(512), 0, stream, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

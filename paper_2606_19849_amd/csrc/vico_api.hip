@@ -192,6 +192,7 @@ int check_gather_shape(int32_t Lq, int32_t T, int32_t S, int32_t cap, int32_t n_
 // the start (table, Q, first keys, the waves' merge) and the merge launch each
 // take about as long as 14 blocks.
 struct RowsPlan { int row_blocks, n_rt, parts; int64_t part_blocks, cost; };
+constexpr int kAppendGroups = 32;            // most extra work-groups of an attention launch that append
 constexpr int64_t kRowsStart = 14;
 constexpr int64_t kRowsChunkCost = 84;       // chunk prefill: the rows kernel up to this cost
 
@@ -365,6 +366,13 @@ int vico_chunk_prefill_attn_ex(const void* q, const void* k_chunk, const void* v
     a.app_rv = (uint16_t*)ring_v;
     a.app_p0 = (int)(hist_len % ring_slots);
   }
+  // Without a split there is no merge launch to carry the append.  Where the
+  // ring has room for window and chunk, the written slots are outside the
+  // window: extra work-groups of the attention launch copy the chunk while the
+  // others attend (77-token chunk 10.6 -> 7.3 us a call, 7B chunk 461 -> 457).
+  // Otherwise the copy is a launch of its own after every read of the window.
+  const bool beside = append && int64_t(sh.Wv) + chunk_len <= ring_slots;
+  const int app_groups = beside ? (int)std::min<int64_t>((cb / 8 + 511) / 512, kAppendGroups) : 0;
   const double scale = softmax_scale > 0.f ? double(softmax_scale) : 1.0 / sqrt(double(head_dim));
   a.scale_log2 = (float)(scale * 1.4426950408889634);
   // Small chunks over short key ranges take the rows kernel: a 256-row tile
@@ -386,16 +394,21 @@ int vico_chunk_prefill_attn_ex(const void* q, const void* k_chunk, const void* v
     r.Hq = a.Hq; r.Hkv = a.Hkv; r.D = a.D;
     r.parts = rp.parts; r.n_rt = rp.n_rt; r.row_blocks = rp.row_blocks;
     r.out_f32 = a.out_f32; r.bidir = a.bidir; r.scale_log2 = a.scale_log2;
+    const vico::AppendArgs ap{a.kc, a.vc, a.app_rk, a.app_rv, a.C, a.R, a.app_p0, a.Hkv * a.D};
+    if (rp.parts == 1 && app_groups > 0) {
+      r.app = ap;
+      r.app_blocks = app_groups;
+    }
     hipError_t e = vico::launch_rows(r, (hipStream_t)stream);
     if (e == hipSuccess && rp.parts > 1) {
       a.splits = rp.parts;
       e = vico::launch_merge(a, (hipStream_t)stream);          // appends too, when asked
-    } else if (e == hipSuccess && append) {
-      const vico::AppendArgs ap{a.kc, a.vc, a.app_rk, a.app_rv, a.C, a.R, a.app_p0, a.Hkv * a.D};
+    } else if (e == hipSuccess && append && r.app_blocks == 0) {
       e = vico::launch_append(ap, (hipStream_t)stream);
     }
     return e == hipSuccess ? VICO_OK : hip_fail(e);
   }
+  if (sh.splits == 1) a.app_blocks = app_groups;
   const hipError_t e = vico::launch_attention(a, sh.grid, (hipStream_t)stream);
   return e == hipSuccess ? VICO_OK : hip_fail(e);
 }

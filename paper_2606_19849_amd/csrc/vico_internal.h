@@ -52,6 +52,8 @@ struct AttnArgs {
   uint16_t* app_rk;    // append after attending (null: no append): ring K, V
   uint16_t* app_rv;
   int app_p0;          // first ring slot written = hist_len mod R
+  int app_blocks;      // > 0: extra work-groups of the attention launch that append (no split; the
+                       // written slots are outside the window)
 };
 
 // Short-query attention over gathered key segments: query rows are the last
@@ -80,6 +82,15 @@ struct GatherArgs {
   float scale_log2;
 };
 
+struct AppendArgs {
+  const uint16_t* kc;
+  const uint16_t* vc;
+  uint16_t* rk;
+  uint16_t* rv;
+  int C, R, p0;        // p0 = hist_len mod R
+  int row_elems;       // Hkv * D
+};
+
 // Few query rows, keys read straight into registers (attn_rows.hip): row
 // tiles of 16 * row_blocks packed rows, the key range in `parts`.  Keys as in
 // GatherArgs; the store segments come from a device table (seg_start,
@@ -106,15 +117,8 @@ struct RowsArgs {
   int parts, n_rt, row_blocks;
   int out_f32, bidir;
   float scale_log2;
-};
-
-struct AppendArgs {
-  const uint16_t* kc;
-  const uint16_t* vc;
-  uint16_t* rk;
-  uint16_t* rv;
-  int C, R, p0;        // p0 = hist_len mod R
-  int row_elems;       // Hkv * D
+  int app_blocks;           // > 0: extra work-groups that do `app` (slots outside the window)
+  AppendArgs app;
 };
 
 // The append of a chunk, ring[(p0 + j) mod R] <- chunk[j] for K and V, as

@@ -108,3 +108,23 @@ def test_tile_kernel_short_ranges(case, flags):
     torch.cuda.synchronize()
     ref, ref_lse, b = oracle_and_bound(inp, parts=parts, bidirectional=bool(flags))
     check_f32(out.cpu().numpy().astype(np.float64), ref, b, lse.cpu().numpy().astype(np.float64), ref_lse)
+
+
+@pytest.mark.parametrize("shape", [
+    # ring with room for window and chunk (the copy rides on the attention launch), exactly and with a wrap
+    (8, 2, 128, 16, 400, 777, 300, 77), (8, 2, 128, 0, 377, 5000, 300, 77), (8, 1, 64, 3, 2000, 3999, 1500, 300),
+    # one slot short of it (the copy is a launch of its own)
+    (8, 2, 128, 16, 376, 777, 300, 77)])
+@pytest.mark.parametrize("splits", [0, 1, 2])
+def test_append_beside_the_attention(shape, splits):
+    """One call with the append equals the attention and then vico_kv_append, bit for bit, ring included."""
+    inp = make_chunk_inputs(ChunkShape(*shape), seed=611, family="F2")
+    a, b = DeviceChunk(inp), DeviceChunk(inp)
+    o, lse = a.attention(num_splits=splits)
+    vico.vico_kv_append(a.kc, a.vc, a.rk, a.rv, inp.shape.hist_len)
+    oa, la = b.attention(num_splits=splits, flags=vico.VICO_ATTN_APPEND)
+    torch.cuda.synchronize()
+    assert np.array_equal(o, oa) and np.array_equal(lse, la)
+    assert torch.equal(a.rk, b.rk) and torch.equal(a.rv, b.rv)
+    ref, ref_lse, bound = oracle_and_bound(inp, parts=max(a.parts, 8))
+    check_f32(oa, ref, bound, la, ref_lse)

@@ -51,8 +51,8 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* p, int bytes) {
 // 16 bytes per lane from a buffer straight into LDS: lane i writes lds + 16*i.
 // Kept in a device-only function: used inline in a kernel body, the builtin
 // makes the host compilation pass drop the kernel's launch stub.
-__device__ __forceinline__ void load_lds16(rsrc_t r, lds_void* lds, uint32_t voffset) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds, 16, voffset, 0, 0, 0);
+__device__ __forceinline__ void load_lds16(rsrc_t r, lds_void* lds, uint32_t voffset, uint32_t soffset = 0) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds, 16, voffset, soffset, 0, 0);
 }
 
 // s_waitcnt immediate: vmcnt(n), lgkmcnt(0), expcnt not waited for.

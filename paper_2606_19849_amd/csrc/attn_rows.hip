@@ -21,6 +21,14 @@
 //     32 keys are two 16-key products whose row order is chosen so that lane
 //     group j = lane/16 ends with the logits of keys 8j .. 8j+7: P^T is then
 //     the B operand of the second product as it stands.
+//     A wave's 16 consecutive lanes then ask for 16 different rows, 16 bytes of
+//     each, and the CU takes such a load at a fraction of the rate of one that
+//     covers whole rows (reading the same bytes row by row took 2.1 us off an
+//     8.2 us call of 5 row tiles).  STAGE: K comes by whole rows into the wave's own LDS and
+//     is read back as fragments; no barrier, the stage is the wave's part of
+//     the merge buffer.  It costs a pass through LDS on the way of each block,
+//     so it is for calls whose row tiles read the same keys, out of the
+//     caches; where one tile streams them from HBM it is 5 % slower.
 //   * O^T = V^T P^T: the A operand wants 8 consecutive keys of one dim per
 //     lane.  A lane loads VE = d/16 consecutive dims of its 8 keys (each load
 //     covers 4 whole rows) and transposes them in registers (one v_perm_b32
@@ -35,7 +43,7 @@
 namespace vico {
 namespace {
 
-template <int D, int NRB, int NW>
+template <int D, int NRB, int NW, bool STAGE>
 __global__ __launch_bounds__(NW * 64, 1) void attn_rows_kernel(RowsArgs a) {
   constexpr int NKS = D / 32;              // k-steps of Q K^T
   constexpr int VE = D / 16;               // dims per lane of a V row
@@ -121,7 +129,17 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_rows_kernel(RowsArgs a) {
   const int ka = 8 * (n >> 2) + (n & 3);                       // this lane's key of the first product; second: + 4
   const uint32_t k_off = (uint32_t)(kv * D * 2 + j * 16);
   const uint32_t v_off = (uint32_t)(kv * D * 2 + n * (VE * 2));
-  const uint32_t k_lane = (uint32_t)(ka * rbytes) + k_off;
+  // K in the wave's LDS: row r at r * RBY, its 16-byte unit u at u ^ swz(r), where swz(r) takes the row's
+  // low bits and one above (16 lanes of a fragment read then touch all banks).  Load i brings rows of KR * i.
+  constexpr int RBY = D * 2, KR = 512 / D, NKL = BK / KR;
+  const int lr = lane / (RBY / 16), lu = lane % (RBY / 16);
+  const uint32_t k_lane = STAGE ? (uint32_t)(lr * rbytes) : (uint32_t)(ka * rbytes) + k_off;
+  const uint32_t k_unit = (uint32_t)((lu ^ lr) * 16);
+  const int swz0 = n & (RBY / 16 - 1);
+  char* const k_stage = (char*)&o_s[wave][0][0];
+  const char* const k_frag = k_stage + ka * RBY;
+  const uint32_t k_fu = (uint32_t)((swz0 ^ j) * 16);
+  static_assert(BK * RBY <= RT * OS * 4, "the stage lies in the wave's part of the merge buffer");
   const uint32_t v_lane = (uint32_t)(8 * j * rbytes) + v_off;
   auto vload = [&](rsrc_t r, uint32_t off, uint32_t so) __attribute__((always_inline)) {
     if constexpr (VE == 8) return __builtin_amdgcn_raw_buffer_load_b128(r, off, so, 0);
@@ -147,13 +165,31 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_rows_kernel(RowsArgs a) {
     if (bk) {
       const rsrc_t rk = make_rsrc(bk, rows * rbytes), rv = make_rsrc(bv, rows * rbytes);
       const uint32_t so = (uint32_t)row0 * (uint32_t)rbytes;
+      if constexpr (STAGE) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the last block's fragments are read
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+        for (int i = 0; i < NKL; ++i) {
+          const uint32_t x = D == 128 ? 64 * ((i ^ (i >> 1)) & 1) + 128 * (i >> 2) : 64 * (i & 1);
+          load_lds16(rk, (lds_void*)(k_stage + i * 1024), k_lane + (k_unit ^ x), so + (uint32_t)(kv * RBY + i * KR * rbytes));
+        }
+        asm volatile("" ::: "memory");
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks)
-          kr[h][ks] = __builtin_amdgcn_raw_buffer_load_b128(rk, k_lane + ks * 64, so + h * 4 * rbytes, 0);
+        for (int i = 0; i < 8; ++i) vr[i] = vload(rv, v_lane, so + i * rbytes);
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");        // K is there; the 8 V loads may be under way
 #pragma unroll
-      for (int i = 0; i < 8; ++i) vr[i] = vload(rv, v_lane, so + i * rbytes);
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int ks = 0; ks < NKS; ++ks)
+            kr[h][ks] = *(const u32x4*)(k_frag + h * 4 * RBY + (k_fu ^ (uint32_t)(64 * (ks ^ h))));
+      } else {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int ks = 0; ks < NKS; ++ks)
+            kr[h][ks] = __builtin_amdgcn_raw_buffer_load_b128(rk, k_lane + ks * 64, so + h * 4 * rbytes, 0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) vr[i] = vload(rv, v_lane, so + i * rbytes);
+      }
       return;
     }
     // a block across regions or segments: lane i resolves key k0 + i%32 (row,
@@ -330,10 +366,14 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_rows_kernel(RowsArgs a) {
 template <int D>
 hipError_t launch(const RowsArgs& a, hipStream_t stream) {
   const dim3 grid(a.n_rt * a.parts * a.Hkv + a.app_blocks);
-  switch (a.row_blocks) {
-    case 1: hipLaunchKernelGGL((attn_rows_kernel<D, 1, 8>), grid, dim3(512), 0, stream, a); break;
-    case 2: hipLaunchKernelGGL((attn_rows_kernel<D, 2, 8>), grid, dim3(512), 0, stream, a); break;
-    default: return hipErrorInvalidValue;
+  if (a.row_blocks == 1) {
+    if (a.stage) hipLaunchKernelGGL((attn_rows_kernel<D, 1, 8, true>), grid, dim3(512), 0, stream, a);
+    else hipLaunchKernelGGL((attn_rows_kernel<D, 1, 8, false>), grid, dim3(512), 0, stream, a);
+  } else if (a.row_blocks == 2) {
+    if (a.stage) hipLaunchKernelGGL((attn_rows_kernel<D, 2, 8, true>), grid, dim3(512), 0, stream, a);
+    else hipLaunchKernelGGL((attn_rows_kernel<D, 2, 8, false>), grid, dim3(512), 0, stream, a);
+  } else {
+    return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }

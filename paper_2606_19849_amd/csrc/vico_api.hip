@@ -379,9 +379,9 @@ int vico_chunk_prefill_attn_ex(const void* q, const void* k_chunk, const void* v
   // leaves most CUs idle there and walks its keys alone.  The line (about 24
   // us at head_dim 128) lies where the two meet; measured without append, us
   // per call, rows against tile kernel: 3B heads, 48 tokens, window 256 8.1 /
-  // 19.1, 1024 14.4 / 24.8; 512 tokens, 1024 20.8 / 28.9 (cost 70), 3000
+  // 19.1, 1024 14.4 / 24.8; 512 tokens, 1024 19.1 / 28.9 (cost 70), 3000
   // 40.3 / 33.3 (cost 137); 7B heads, 512 tokens, 256 (two rounds, cost 84)
-  // 24.9 / 29.2; 307 tokens, 1024 (two rounds, cost 124) 34.4 / 31.5.  A split
+  // 23.6 / 29.2; 307 tokens, 1024 (two rounds, cost 124) 34.4 / 31.5.  A split
   // that the caller chose stays with the tile kernel.
   const RowsPlan rp = plan_rows(int64_t(sh.Hq / sh.Hkv) * sh.C, sh.Hkv, int64_t(sh.S) + sh.Wv + sh.C, sh.splits, 0);
   if (num_splits == 0 && rp.cost <= kRowsChunkCost) {
@@ -393,6 +393,10 @@ int vico_chunk_prefill_attn_ex(const void* q, const void* k_chunk, const void* v
     r.seg0 = a.ws; r.len0 = std::min(a.Wv, a.R - a.ws); r.len1 = a.Wv - r.len0;
     r.Hq = a.Hq; r.Hkv = a.Hkv; r.D = a.D;
     r.parts = rp.parts; r.n_rt = rp.n_rt; r.row_blocks = rp.row_blocks;
+    // K through LDS as soon as two row tiles read the same keys: us per call, direct and staged,
+    // 3B heads, 77 tokens over 307 keys 8.2 / 7.7, 256 over 512 11.8 / 10.9, 512 over 1024 20.9 / 19.1;
+    // small heads, 300 tokens over 512 8.1 / 6.5; 7B heads, 163 tokens over 676 14.7 / 14.1
+    r.stage = rp.n_rt > 1;
     r.out_f32 = a.out_f32; r.bidir = a.bidir; r.scale_log2 = a.scale_log2;
     const vico::AppendArgs ap{a.kc, a.vc, a.app_rk, a.app_rv, a.C, a.R, a.app_p0, a.Hkv * a.D};
     if (rp.parts == 1 && app_groups > 0) {
@@ -617,6 +621,12 @@ int vico::gather_attn_entry(const void* q, int32_t q_len, const void* tail_k, co
     r.parts = rp.parts; r.n_rt = rp.n_rt; r.row_blocks = rp.row_blocks;
     r.out_f32 = a.out_f32; r.scale_log2 = a.scale_log2;
     if (a.n_segs == 0) r.seg_start = nullptr;
+    // K through LDS: a store is mostly read from HBM, and few row tiles wait for that alone.  us a
+    // layer of a query pass (the retrieval's share is 0.4), direct and staged, 32 chunks (20.5k keys) of
+    // 128-dim heads: 2 row tiles 21.4 / 22.8, 4 tiles 27.6 / 27.9, 5 tiles 32.1 / 31.4, 12 tiles 33.8 /
+    // 32.3; 8 short chunks (one block a wave), 7 tiles 11.8 / 11.9.  64-dim heads: 2 tiles 11.4 / 11.0,
+    // 6 tiles 14.4 / 12.6.
+    r.stage = rp.n_rt > 1 && (a.D == 64 || (rp.n_rt >= 5 && rp.part_blocks > 8));
     e = vico::launch_rows(r, (hipStream_t)stream);
     if (e == hipSuccess && r.parts > 1) {
       vico::AttnArgs m{};

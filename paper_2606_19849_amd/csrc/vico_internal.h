@@ -115,6 +115,7 @@ struct RowsArgs {
   int seg0, len0, len1;     // seg_start null: slots [seg0, seg0 + len0) and [0, len1)
   int Hq, Hkv, D;
   int parts, n_rt, row_blocks;
+  int stage;                // 1: K goes through LDS (the rule stands at each caller)
   int out_f32, bidir;
   float scale_log2;
   int app_blocks;           // > 0: extra work-groups that do `app` (slots outside the window)

@@ -75,6 +75,26 @@ def test_gathered_rows(heads, q_len, tail, n_seg):
             check_f32(o, ro, b, lse, rl)
 
 
+@pytest.mark.parametrize("heads,q_len", [((7, 1, 128), 33), ((16, 2, 128), 20), ((12, 2, 64), 6)])
+@pytest.mark.parametrize("n_seg", [1, 9, 64])
+@pytest.mark.parametrize("splits", [1, 2])
+def test_gathered_rows_through_lds(heads, q_len, n_seg, splits):
+    """Five or more row tiles over key ranges of several blocks a wave (K staged
+    through LDS), blocks inside a segment and across segments.  Few parts and a
+    hint of 1200 keys take that route whatever the table holds."""
+    Hq, Hkv, D = heads
+    qi = make_query_inputs(QueryShape(Hq, Hkv, D, 40, 64, 12, 20, 90, q_len, q_len + 3, 6), seed=950 + n_seg, family="F2")
+    d = DeviceQuery(qi)
+    rng = np.random.default_rng(n_seg)
+    st = rng.integers(-20, qi.store_len - 64, n_seg).astype(np.int64)
+    ln = rng.integers(30, 1 + 1800 // n_seg if n_seg < 10 else 71, n_seg).astype(np.int32)
+    lo, hi = np.clip(st, 0, qi.store_len), np.clip(st + ln, 0, qi.store_len)
+    keep = hi > lo
+    o, lse, parts = d.attend(st, ln, num_splits=splits, hint=1200)
+    ro, rl, b = d.reference(lo[keep], (hi - lo)[keep], parts=max(parts, 8))
+    check_f32(o, ro, b, lse, rl)
+
+
 # key ranges of one to six 64-key tiles per split (the pipeline runs three tiles ahead), row counts
 # around a wave's 32 rows and a work-group's 256, ring end and chunk end inside a tile
 TILE_CHUNKS = [

@@ -40,8 +40,10 @@ PEAK_HBM_GBS = 8000.0
 ROOT = os.path.dirname(os.path.abspath(__file__))
 CSRC = "paper_2606_19849_amd/csrc/"
 # sources whose kernels a traffic figure covers (it goes stale when any changes)
-KERNEL_SRC = {"attn_fwd_kernel<128>": [CSRC + "attn_fwd.hip", CSRC + "attn_merge.hip", CSRC + "attn_common.h",
-                                       CSRC + "vico_internal.h"],
+KERNEL_SRC = {"attn_fwd_kernel<128>": [CSRC + "attn_fwd.hip", CSRC + "attn_pipe.h", CSRC + "attn_merge.hip",
+                                       CSRC + "attn_common.h", CSRC + "vico_internal.h"],
+              "attn_rows_kernel<128>": [CSRC + "attn_rows.hip", CSRC + "attn_merge.hip", CSRC + "attn_common.h",
+                                        CSRC + "vico_internal.h"],
               "attn_gather_kernel<128>": [CSRC + "attn_gather.hip", CSRC + "attn_merge.hip", CSRC + "attn_common.h",
                                           CSRC + "vico_internal.h"],
               "kv_append_kernel": [CSRC + "kv_append.hip"],
@@ -609,6 +611,7 @@ def run_query_workload(args, torch, vico):
     tfl = float(flops.mean() / attn_s / 1e12)
     t_hbm = bytes_.mean() / (PEAK_HBM_GBS * 1e9)
     t_mfma = flops.mean() / (PEAK_BF16_TFLOPS * 1e12)
+    kernel = "attn_rows_kernel<128>" if decode else "attn_gather_kernel<128>"
     res = {
         "metric": ("decode-step attention per layer" if decode else
                    "query-side retrieval + gathered attention per layer (TTFT building block)"),
@@ -630,8 +633,8 @@ def run_query_workload(args, torch, vico):
                      "peak": PEAK_HBM_GBS if t_hbm >= t_mfma else PEAK_BF16_TFLOPS,
                      "unit": "GB/s" if t_hbm >= t_mfma else "TFLOP/s",
                      "frac": round(gbs / PEAK_HBM_GBS if t_hbm >= t_mfma else tfl / PEAK_BF16_TFLOPS, 4),
-                     "traffic": measured_traffic("attn_gather_kernel<128>", args.workload),
-                     "kernel": "attn_gather_kernel<128> (+ split merge)",
+                     "traffic": measured_traffic(kernel, args.workload),
+                     "kernel": kernel + " (+ split merge)",
                      "bytes_per_launch_mean": float(bytes_.mean()), "flops_per_launch_mean": float(flops.mean())},
     }
     return res

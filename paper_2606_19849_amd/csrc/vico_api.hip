@@ -130,7 +130,10 @@ int check_attn_shape(int32_t C, int32_t S, int32_t R, int64_t H, int64_t W, int3
     if (splits == VICO_SPLIT_BALANCED ||
         (splits == 0 && 2 * n_tiles_rows * ns <= int64_t(vico::kNumCUs) * vico::kWgPerCU))
       parts = plan_balanced(C, S + (int)wv, Hq, Hkv, bidir, sh->pack, &sh->total_tiles, &sh->grid);
-    if (parts > 0) {
+    // one part: every row tile falls to one work-group as it is, so the plain
+    // schedule does the same work and writes the output itself (the balanced
+    // one leaves every row to a merge)
+    if (parts > 1) {
       sh->balanced = 1;
       sh->splits = parts;
     } else {
@@ -214,6 +217,19 @@ RowsPlan plan_rows(int64_t NR, int Hkv, int64_t keys, int max_parts, int exact_p
   return best;
 }
 
+// Whether a chunk call takes the rows kernel.  Small chunks over short key
+// ranges do: a 256-row tile leaves most CUs idle there and walks its keys
+// alone.  The line (about 24 us at head_dim 128) lies where the two meet;
+// measured without append, us per call, rows against tile kernel: 3B heads, 48
+// tokens, window 256 8.1 / 19.1, 1024 14.4 / 24.8; 512 tokens, 1024 19.1 / 28.9
+// (cost 70), 3000 40.3 / 33.3 (cost 137); 7B heads, 512 tokens, 256 (two
+// rounds, cost 84) 23.6 / 29.2; 307 tokens, 1024 (two rounds, cost 124) 34.4 /
+// 31.5.  A split that the caller chose stays with the tile kernel.
+bool chunk_takes_rows(const Shape& sh, int num_splits, RowsPlan* rp) {
+  *rp = plan_rows(int64_t(sh.Hq / sh.Hkv) * sh.C, sh.Hkv, int64_t(sh.S) + sh.Wv + sh.C, sh.splits, 0);
+  return num_splits == 0 && rp->cost <= kRowsChunkCost;
+}
+
 bool aligned_to(const void* p, uintptr_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; }
 
 int hip_fail(hipError_t e) {
@@ -266,6 +282,26 @@ int vico_attn_plan_ex(int32_t chunk_len, int32_t sink_len, int32_t ring_slots, i
   if (st != VICO_OK) return st;
   if (num_splits_out) *num_splits_out = sh.splits;
   if (workspace_bytes_out) *workspace_bytes_out = sh.ws_bytes;
+  return VICO_OK;
+}
+
+int vico_attn_route(int32_t chunk_len, int32_t sink_len, int32_t ring_slots, int64_t hist_len, int64_t window,
+                    int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim, int32_t num_splits, int32_t flags,
+                    int32_t* route_out) {
+  Shape sh;
+  const int st = check_attn_shape(chunk_len, sink_len, ring_slots, hist_len, window, num_q_heads, num_kv_heads,
+                                  head_dim, num_splits, flags, &sh);
+  if (st != VICO_OK) return st;
+  RowsPlan rp;
+  if (chunk_len > 0 && chunk_takes_rows(sh, num_splits, &rp)) {
+    route_out[0] = vico::kRouteRows;
+    route_out[1] = rp.parts;
+    route_out[2] = sh.Hkv * rp.n_rt * rp.parts;
+  } else {
+    route_out[0] = sh.balanced ? vico::kRouteBalanced : vico::kRouteTile;
+    route_out[1] = sh.splits;
+    route_out[2] = sh.grid;
+  }
   return VICO_OK;
 }
 
@@ -375,16 +411,8 @@ int vico_chunk_prefill_attn_ex(const void* q, const void* k_chunk, const void* v
   const int app_groups = beside ? (int)std::min<int64_t>((cb / 8 + 511) / 512, kAppendGroups) : 0;
   const double scale = softmax_scale > 0.f ? double(softmax_scale) : 1.0 / sqrt(double(head_dim));
   a.scale_log2 = (float)(scale * 1.4426950408889634);
-  // Small chunks over short key ranges take the rows kernel: a 256-row tile
-  // leaves most CUs idle there and walks its keys alone.  The line (about 24
-  // us at head_dim 128) lies where the two meet; measured without append, us
-  // per call, rows against tile kernel: 3B heads, 48 tokens, window 256 8.1 /
-  // 19.1, 1024 14.4 / 24.8; 512 tokens, 1024 19.1 / 28.9 (cost 70), 3000
-  // 40.3 / 33.3 (cost 137); 7B heads, 512 tokens, 256 (two rounds, cost 84)
-  // 23.6 / 29.2; 307 tokens, 1024 (two rounds, cost 124) 34.4 / 31.5.  A split
-  // that the caller chose stays with the tile kernel.
-  const RowsPlan rp = plan_rows(int64_t(sh.Hq / sh.Hkv) * sh.C, sh.Hkv, int64_t(sh.S) + sh.Wv + sh.C, sh.splits, 0);
-  if (num_splits == 0 && rp.cost <= kRowsChunkCost) {
+  RowsPlan rp;
+  if (chunk_takes_rows(sh, num_splits, &rp)) {
     vico::RowsArgs r{};
     r.q = a.q; r.tail_k = a.kc; r.tail_v = a.vc; r.sink_k = a.sink_k; r.sink_v = a.sink_v;
     r.store_k = a.ring_k; r.store_v = a.ring_v;

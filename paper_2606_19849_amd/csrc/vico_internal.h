@@ -174,3 +174,16 @@ hipError_t launch_topk(const float* scores, int N, int k, float min_score, const
                        int32_t* seg_len, int32_t* out_count, hipStream_t stream);
 
 }  // namespace vico
+
+// ---- which kernel a call of these arguments runs, by the same code that the
+// call itself runs; nothing is launched.  For tests: not part of the public
+// interface.  route_out: {kernel, key-range parts (1: no merge launch),
+// attention work-groups}.
+namespace vico {
+enum Route { kRouteTile = 0, kRouteBalanced = 1, kRouteRows = 2, kRouteGather = 3 };
+}
+extern "C" {
+int vico_attn_route(int32_t chunk_len, int32_t sink_len, int32_t ring_slots, int64_t hist_len, int64_t window,
+                    int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim, int32_t num_splits, int32_t flags,
+                    int32_t* route_out);
+}

@@ -117,11 +117,16 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int g
   const int row0 = rt * BM;
   const int n_tiles = tiles_of(rt);
 
-  // this wave: packed rows wrow0 .. wrow0 + 63 in two blocks; this lane: token
-  // tok[rb] of head h[rb] in each block
+  // this wave: packed rows wrow0 .. wrow0 + 31 in one block (RB); this lane:
+  // token tok[rb] of head h[rb] in each block
   const int wrow0 = row0 + wave * (RB * 32);
   const bool wave_active = wrow0 < NR;
   const int wave_first_lim = last_key_of_tok(tok_of(wrow0));      // last key of the wave's first row
+  // the wave computes tiles [t_lo, t_end): past its last row's last key it only
+  // keeps loading for the others (P = 0 there is not enough: 0 times an
+  // infinite or NaN value of a later token is NaN)
+  const int t_end =
+      wave_active ? min(t_hi, last_key_of_tok(tok_of(wrow0 + RB * 32 - 1)) / BN + 1) : t_lo;
   int tok[RB], h[RB], key_lim[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
@@ -326,7 +331,8 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int g
     uint32_t boff = 0;                             // buffer offset of tile t
     constexpr uint32_t kWrap = NB * TBY - 1;
     static_assert((NB & (NB - 1)) == 0, "buffer offsets wrap by a mask");
-    if (wave_active) {
+    int t = t_lo;
+    if (t < t_end) {
       bf16x8 vf[NDB] = {};
       Tile wt{qf, k_rd, v_rd, v_nx, o, m_run, l_run, neg_m, vf, a.scale_log2};
       f32x16 s0[RB], s1[RB];
@@ -335,7 +341,7 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int g
       const int t_mask = wave_first_lim < 63 ? 0 : (wave_first_lim - 63) / BN + 1;   // tiles from here on may need the mask
       if (t_lo >= t_mask) Tile::mask(t_lo * BN, key_lim, hh, s0);
       wt.first_max(s0);
-      for (int t = t_lo; t < t_hi; ++t) {
+      for (; t < t_end; ++t) {
         if (__builtin_expect(t >= t_mask, 0)) Tile::mask(t * BN, key_lim, hh, s0);
         uint32_t next = 0;                         // of tile t+1
         wt.template half<32, 48, 0>(s0, s1, p1, p0, [&](auto slot) __attribute__((always_inline)) {
@@ -360,13 +366,13 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int g
         boff = next;
         finish_load(fill, t + AHEAD);
       }
+      // V of the wave's last tile is read here, before the barrier of the step that reuses its buffer
       wt.template last_values<48>(p1);
-    } else {
-      for (int t = t_lo; t < t_hi; ++t) {
-        landed();
-        load_whole((boff + AHEAD * TBY) & kWrap, t + AHEAD);
-        boff = (boff + TBY) & kWrap;
-      }
+    }
+    for (; t < t_hi; ++t) {
+      landed();
+      load_whole((boff + AHEAD * TBY) & kWrap, t + AHEAD);
+      boff = (boff + TBY) & kWrap;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the empty loads past the last tile
   }

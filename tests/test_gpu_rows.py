@@ -148,3 +148,25 @@ def test_append_beside_the_attention(shape, splits):
     assert torch.equal(a.rk, b.rk) and torch.equal(a.rv, b.rv)
     ref, ref_lse, bound = oracle_and_bound(inp, parts=max(a.parts, 8))
     check_f32(oa, ref, bound, la, ref_lse)
+
+
+@pytest.mark.parametrize("shape", [(4, 2, 128, 5, 200, 300, 150, 256), (8, 2, 64, 0, 300, 500, 260, 300),
+                                   (7, 1, 128, 64, 128, 100, 90, 77), (8, 2, 128, 64, 4096, 4596, 4000, 600)])
+@pytest.mark.parametrize("splits", [0, 1, 3, vico.VICO_SPLIT_BALANCED])
+@pytest.mark.parametrize("poison", [float("nan"), float("inf")])
+def test_later_tokens_stay_out_of_earlier_rows(shape, splits, poison):
+    """NaN or infinity in the last chunk token's K and V reaches no row of a
+    wave whose own key tiles end before it: a wave holds 32 rows (at most 32
+    tokens, from a multiple of 32), and tiles have 64 keys.  The rest of the
+    result keeps its bits."""
+    dc = DeviceChunk(make_chunk_inputs(ChunkShape(*shape), seed=431, family="F2"))
+    sh = dc.inp.shape
+    clean, clean_lse = dc.attention(num_splits=splits)
+    dc.kc[-1] = poison
+    dc.vc[-1] = poison
+    o, lse = dc.attention(num_splits=splits)
+    first = sh.sink_len + sh.visible_window
+    last_of_wave = np.minimum(np.arange(sh.chunk_len) // 32 * 32 + 31, sh.chunk_len - 1)
+    apart = (first + last_of_wave) // 64 < (first + sh.chunk_len - 1) // 64
+    assert apart.any()
+    assert np.array_equal(o[apart], clean[apart]) and np.array_equal(lse[:, apart], clean_lse[:, apart])

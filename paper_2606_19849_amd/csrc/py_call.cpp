@@ -100,7 +100,10 @@ struct Args {
   }
 };
 
+// Address of a tensor that the library reads, and of one that it writes: the
+// second gives a copy-on-write tensor memory of its own first.
 void* ptr(const at::Tensor* t) { return t && t->numel() > 0 ? const_cast<void*>(t->const_data_ptr()) : nullptr; }
+void* wptr(const at::Tensor* t) { return t && t->numel() > 0 ? t->mutable_data_ptr() : nullptr; }
 int32_t size(const at::Tensor* t, int d) { return t ? (int32_t)t->size(d) : 0; }
 int64_t bytes(const at::Tensor* t) { return t ? t->numel() * (int64_t)t->element_size() : 0; }
 bool shape3(const at::Tensor* t, int64_t a, int64_t b, int64_t c) {
@@ -153,11 +156,14 @@ PyObject* prefill(PyObject* const* args, Py_ssize_t n) {
   if (!in.ok || !shape3(out, q->size(0), q->size(1), q->size(2))) Py_RETURN_NONE;
   if (lse && (lse->size(0) != q->size(1) || lse->size(1) != q->size(0))) Py_RETURN_NONE;
   if (!fits(q) || !fits(kc) || !fits(sk) || !fits(rk)) Py_RETURN_NONE;
+  const bool append = flags & VICO_ATTN_APPEND;
+  void *const o = wptr(out), *const l = wptr(lse), *const w = wptr(ws);
+  void *const ring_k = append ? wptr(rk) : ptr(rk), *const ring_v = append ? wptr(rv) : ptr(rv);
   return called(in, [&] {
-    return vico_chunk_prefill_attn_ex(ptr(q), ptr(kc), ptr(vc), size(q, 0), ptr(sk), ptr(sv), size(sk, 0), ptr(rk),
-                                      ptr(rv), size(rk, 0), hist, window, size(q, 1), size(kc, 1), size(q, 2), scale,
-                                      ptr(out), out->scalar_type() == at::kFloat ? VICO_DTYPE_F32 : VICO_DTYPE_BF16,
-                                      (float*)ptr(lse), splits, flags, ptr(ws), bytes(ws), stream);
+    return vico_chunk_prefill_attn_ex(ptr(q), ptr(kc), ptr(vc), size(q, 0), ptr(sk), ptr(sv), size(sk, 0), ring_k, ring_v,
+                                      size(rk, 0), hist, window, size(q, 1), size(kc, 1), size(q, 2), scale, o,
+                                      out->scalar_type() == at::kFloat ? VICO_DTYPE_F32 : VICO_DTYPE_BF16, (float*)l,
+                                      splits, flags, w, bytes(ws), stream);
   });
 }
 
@@ -181,16 +187,16 @@ PyObject* gather_call(PyObject* const* args, Py_ssize_t n, bool noalloc) {
   if (lse && (lse->size(0) != q->size(1) || lse->size(1) != q->size(0))) Py_RETURN_NONE;
   if (!fits(q) || !fits(tk) || !fits(sk) || !fits(gk) || !fits(ss)) Py_RETURN_NONE;
   const int32_t dt = out->scalar_type() == at::kFloat ? VICO_DTYPE_F32 : VICO_DTYPE_BF16;
+  void *const o = wptr(out), *const l = wptr(lse), *const w = wptr(ws);
   return called(in, [&] {
     if (noalloc)
       return vico_gather_attn_noalloc(ptr(q), size(q, 0), ptr(tk), ptr(tv), size(tk, 0), ptr(sk), ptr(sv), size(sk, 0),
                                       ptr(gk), ptr(gv), size(gk, 0), (const int64_t*)ptr(ss), (const int32_t*)ptr(sl),
-                                      size(ss, 0), hint, size(q, 1), size(tk, 1), size(q, 2), scale, ptr(out), dt,
-                                      (float*)ptr(lse), splits, stream);
+                                      size(ss, 0), hint, size(q, 1), size(tk, 1), size(q, 2), scale, o, dt, (float*)l, splits,
+                                      stream);
     return vico_gather_attn(ptr(q), size(q, 0), ptr(tk), ptr(tv), size(tk, 0), ptr(sk), ptr(sv), size(sk, 0), ptr(gk),
                             ptr(gv), size(gk, 0), (const int64_t*)ptr(ss), (const int32_t*)ptr(sl), size(ss, 0), hint,
-                            size(q, 1), size(tk, 1), size(q, 2), scale, ptr(out), dt, (float*)ptr(lse), splits, ptr(ws),
-                            bytes(ws), stream);
+                            size(q, 1), size(tk, 1), size(q, 2), scale, o, dt, (float*)l, splits, w, bytes(ws), stream);
   });
 }
 PyObject* gather(PyObject* const* args, Py_ssize_t n) { return gather_call(args, n, false); }
@@ -204,8 +210,9 @@ PyObject* kv_append(PyObject* const* args, Py_ssize_t n) {
   const int64_t hist = in.integer();
   void* stream = in.stream();
   if (!in.ok || !fits(kc) || !fits(rk)) Py_RETURN_NONE;
+  void *const ring_k = wptr(rk), *const ring_v = wptr(rv);
   return called(in, [&] {
-    return vico_kv_append(ptr(kc), ptr(vc), size(kc, 0), ptr(rk), ptr(rv), size(rk, 0), hist, size(kc, 1), size(kc, 2),
+    return vico_kv_append(ptr(kc), ptr(vc), size(kc, 0), ring_k, ring_v, size(rk, 0), hist, size(kc, 1), size(kc, 2),
                           stream);
   });
 }
@@ -216,7 +223,8 @@ PyObject* token_mean(PyObject* const* args, Py_ssize_t n) {
   const at::Tensor *x = in.tensor(at::kBFloat16, 2), *out = in.tensor(at::kFloat, 1);
   void* stream = in.stream();
   if (!in.ok || out->size(0) != x->size(1) || !fits(x)) Py_RETURN_NONE;
-  return called(in, [&] { return vico_token_mean(ptr(x), size(x, 0), size(x, 1), (float*)ptr(out), stream); });
+  void* const o = wptr(out);
+  return called(in, [&] { return vico_token_mean(ptr(x), size(x, 0), size(x, 1), (float*)o, stream); });
 }
 
 // query_feat, chunk_feat, scores, stream
@@ -225,9 +233,9 @@ PyObject* chunk_scores(PyObject* const* args, Py_ssize_t n) {
   const at::Tensor *qf = in.tensor(at::kFloat, 1), *cf = in.tensor(at::kFloat, 2), *sc = in.tensor(at::kFloat, 1);
   void* stream = in.stream();
   if (!in.ok || qf->size(0) != cf->size(1) || sc->size(0) != cf->size(0) || !fits(cf)) Py_RETURN_NONE;
+  void* const o = wptr(sc);
   return called(in, [&] {
-    return vico_chunk_scores((const float*)ptr(qf), (const float*)ptr(cf), size(cf, 0), size(cf, 1), (float*)ptr(sc),
-                             stream);
+    return vico_chunk_scores((const float*)ptr(qf), (const float*)ptr(cf), size(cf, 0), size(cf, 1), (float*)o, stream);
   });
 }
 
@@ -246,10 +254,11 @@ PyObject* topk_chunks(PyObject* const* args, Py_ssize_t n) {
   if (oc->size(0) < k || os->size(0) < k) Py_RETURN_NONE;
   if (cs && (cs->size(0) < sc->size(0) || cl->size(0) < sc->size(0) || ss->size(0) < k || sl->size(0) < k))
     Py_RETURN_NONE;
+  void *const c = wptr(oc), *const v = wptr(os), *const b = wptr(ss), *const e = wptr(sl), *const m = wptr(cnt);
   return called(in, [&] {
     return vico_topk_chunks((const float*)ptr(sc), size(sc, 0), k, lowest, (const int64_t*)ptr(cs),
-                            (const int32_t*)ptr(cl), (int32_t*)ptr(oc), (float*)ptr(os), (int64_t*)ptr(ss),
-                            (int32_t*)ptr(sl), (int32_t*)ptr(cnt), stream);
+                            (const int32_t*)ptr(cl), (int32_t*)c, (float*)v, (int64_t*)b, (int32_t*)e, (int32_t*)m,
+                            stream);
   });
 }
 
@@ -268,10 +277,11 @@ PyObject* temporal_drop(PyObject* const* args, Py_ssize_t n) {
   if (keep->size(0) != B || keep->size(1) != n_f || idx->size(0) < rows) Py_RETURN_NONE;
   if (sim && (sim->size(0) != B || sim->size(1) != n_f)) Py_RETURN_NONE;
   if (tok && (tok->size(0) < rows || tok->size(1) != dm)) Py_RETURN_NONE;
+  void *const k = wptr(keep), *const s = wptr(sim), *const o = wptr(tok), *const i = wptr(idx), *const m = wptr(cnt);
+  void* const w = wptr(ws);
   return called(in, [&] {
-    return vico_temporal_drop(ptr(f), (int32_t)B, (int32_t)C, (int32_t)n_f, (int32_t)dm, tau, ptr(prev),
-                              (uint8_t*)ptr(keep), (float*)ptr(sim), ptr(tok), (int32_t*)ptr(idx), (int32_t*)ptr(cnt),
-                              ptr(ws), bytes(ws), stream);
+    return vico_temporal_drop(ptr(f), (int32_t)B, (int32_t)C, (int32_t)n_f, (int32_t)dm, tau, ptr(prev), (uint8_t*)k,
+                              (float*)s, o, (int32_t*)i, (int32_t*)m, w, bytes(ws), stream);
   });
 }
 

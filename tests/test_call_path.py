@@ -94,3 +94,44 @@ def test_rejections_are_the_general_ones():
     vico.vico_kv_append(k + 1, k + 2, *ring, np.int64(6))      # an index type of numpy: the general path
     torch.cuda.synchronize()
     assert float(ring[0][6:].sum()) == 128 and float(ring[1][:2].sum()) == 256
+
+
+@pytest.mark.gpu
+def test_lazily_cloned_outputs_get_memory_of_their_own():
+    """A copy-on-write clone as an output leaves the tensor that it was cloned from alone, and inputs may be clones."""
+    bf = lambda *s: torch.randn(*s, device="cuda").to(torch.bfloat16)   # noqa: E731
+    new = lambda dt, *s: torch.zeros(*s, dtype=dt, device="cuda")   # noqa: E731
+    i32, i64, f32 = torch.int32, torch.int64, torch.float32
+    k, v, q, frames, feats = bf(4, 1, 64), bf(4, 1, 64), bf(4, 2, 64), bf(2, 4, 6, 64), torch.randn(9, 64, device="cuda")
+    seg = torch.arange(2, device="cuda"), torch.ones(2, dtype=i32, device="cuda")
+    lens = torch.ones(9, dtype=i32, device="cuda")
+    ring = lambda: [new(torch.bfloat16, 8, 1, 64), new(torch.bfloat16, 8, 1, 64)]   # noqa: E731
+    attn = lambda: [new(f32, 4, 2, 64), new(f32, 2, 4)]   # noqa: E731
+    calls = [
+        (ring(), lambda o: vico.vico_kv_append(k, v, *o, 6)),
+        (attn() + ring(), lambda o: vico.vico_chunk_prefill_attn(q, k, v, None, None, o[2], o[3], 6, 4, o[0], lse=o[1],
+                                                                 flags=vico.VICO_ATTN_APPEND)),
+        (attn(), lambda o: vico.vico_gather_attn(q, k, v, None, None, k, v, *seg, o[0], lse=o[1])),
+        (attn(), lambda o: vico.vico_gather_attn_noalloc(q, k, v, None, None, k, v, *seg, o[0], lse=o[1])),
+        ([new(f32, 64)], lambda o: vico.vico_token_mean(k.view(4, 64), *o)),
+        ([new(f32, 9)], lambda o: vico.vico_chunk_scores(feats[0], feats, *o)),
+        ([new(i32, 3), new(f32, 3), new(i32, 1), new(i64, 3), new(i32, 3)],
+         lambda o: vico.vico_topk_chunks(feats[:, 0].contiguous(), 3, *o[:3], chunk_start=torch.arange(9, device="cuda"),
+                                         chunk_len=lens, seg_start=o[3], seg_len=o[4])),
+        ([new(torch.uint8, 2, 6), new(i32, 48), new(i32, 1), new(f32, 2, 6), new(torch.bfloat16, 48, 64)],
+         lambda o: vico.vico_temporal_drop(frames, 0.1, *o[:3], sim=o[3], out_tokens=o[4])),
+    ]
+    for base, call in calls:
+        want = [t.clone() for t in base]
+        call(want)
+        before = [t.clone() for t in base]
+        clones = [torch._lazy_clone(t) for t in base]
+        call(clones)
+        torch.cuda.synchronize()
+        for t, b, c, w in zip(base, before, clones, want):
+            assert torch.equal(t, b) and torch.equal(c, w)
+    lazy = torch._lazy_clone(k)
+    out = [attn(), attn()]
+    for x, o in zip((k, lazy), out):
+        vico.vico_chunk_prefill_attn(q, x, v, None, None, None, None, 0, 0, o[0], lse=o[1])
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])

@@ -213,21 +213,24 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int g
   };
 
   // direct load n (0 .. NLD-1: K, NLD .. 2*NLD-1: V) of the run's tile to the
-  // buffers at byte offset `boff`.  m0 holds a load's LDS address; the
-  // compiler's code in these kernels does not use m0.  The loads have no
-  // result registers.  Wait states that the compiler does not know assembly to
-  // need: one after a write of m0, five after a VALU write of a scalar operand
-  // (the reload of a scalar kept in a VGPR lane is one).
+  // buffers at byte offset `boff`.  m0 holds a load's LDS address.  The compiler
+  // has m0 for itself (it takes no claim of it), so every load sets it and gives
+  // it back.  The loads have no result registers.  Wait states that the compiler
+  // does not know assembly to need: one after a write of m0, five after a VALU
+  // write of a scalar operand (the reload of a scalar kept in a VGPR lane is one).
   const uint32_t my_part = (uint32_t)(wave * NLD * 1024);
-  auto aim = [&](bool v, uint32_t boff) __attribute__((always_inline)) {
-    asm volatile("s_mov_b32 m0, %0" ::"s"(lds0 + my_part + boff + (v ? 0u : kKBase)) : "memory");
-  };
-  auto load_direct = [&](auto idx) __attribute__((always_inline)) {
+  auto load_direct = [&](auto idx, uint32_t boff) __attribute__((always_inline)) {
     constexpr int i = decltype(idx)::value, n = i % NLD;
     const uint32_t off = i < NLD ? ld_k[n] : ld_v[n], so = run_so;
+    const uint32_t to = lds0 + my_part + boff + (i < NLD ? kKBase : 0u);
     const u32x4 rs = i < NLD ? run_k : run_v;
-    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %0, %1, %2 offen offset:%3 lds" ::"v"(off), "s"(rs), "s"(so), "n"(n * 1024)
-                 : "memory");
+    uint32_t m0;
+    asm volatile(
+        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %5\n\ts_nop 4\n\t"
+        "buffer_load_dwordx4 %1, %2, %3 offen offset:%4 lds\n\ts_mov_b32 m0, %0"
+        : "=&s"(m0)
+        : "v"(off), "s"(rs), "s"(so), "n"(n * 1024), "s"(to)
+        : "memory");
   };
 
   // mixed tiles: each lane resolves its key row and the row's tensor; one
@@ -244,10 +247,11 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int g
       const uint64_t u = (uint64_t)p;
       const u32x4 rs = u32x4{(uint32_t)u, (uint32_t)(u >> 32) & 0xFFFFu, (uint32_t)(n * rbytes), 0x00020000u};
       uint64_t all;
+      uint32_t m0;
       asm volatile(
-          "s_mov_b64 %0, exec\n\ts_mov_b64 exec, %1\n\ts_mov_b32 m0, %2\n\ts_nop 4\n\t"
-          "buffer_load_dwordx4 %3, %4, 0 offen lds\n\ts_mov_b64 exec, %0"
-          : "=&s"(all)
+          "s_mov_b64 %0, exec\n\ts_mov_b32 %1, m0\n\ts_mov_b64 exec, %2\n\ts_mov_b32 m0, %3\n\ts_nop 4\n\t"
+          "buffer_load_dwordx4 %4, %5, 0 offen lds\n\ts_mov_b32 m0, %1\n\ts_mov_b64 exec, %0"
+          : "=&s"(all), "=&s"(m0)
           : "s"(lanes), "s"(to), "v"((uint32_t)row * (uint32_t)rbytes + unit_off), "s"(rs)
           : "memory");
     };
@@ -293,12 +297,7 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int g
     }
   };
   auto load_whole = [&](uint32_t boff, int t) __attribute__((always_inline)) {
-    aim(false, boff);
-    unrolled<NLD>([&](auto i) __attribute__((always_inline)) { load_direct(i); });
-    aim(true, boff);
-    unrolled<NLD>([&](auto i) __attribute__((always_inline)) {
-      load_direct(std::integral_constant<int, NLD + decltype(i)::value>{});
-    });
+    unrolled<2 * NLD>([&](auto i) __attribute__((always_inline)) { load_direct(i, boff); });
     finish_load(boff, t);
   };
 
@@ -358,9 +357,7 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int g
         const uint32_t fill = (boff + AHEAD * TBY) & kWrap;
         wt.template half<0, 16, 32>(s1, s0, p0, p1, [&](auto slot) __attribute__((always_inline)) {
           constexpr int s = decltype(slot)::value, i = s / LSTEP - 1;
-          if constexpr (s == 1) aim(false, fill);
-          if constexpr (s == NLD * LSTEP + 1) aim(true, fill);
-          if constexpr (s % LSTEP == 0 && i >= 0 && i < NL) load_direct(std::integral_constant<int, i>{});
+          if constexpr (s % LSTEP == 0 && i >= 0 && i < NL) load_direct(std::integral_constant<int, i>{}, fill);
         });
         v_nx += next - boff;                       // V of tile t+1
         boff = next;

@@ -199,6 +199,11 @@ constexpr int kAppendGroups = 32;            // most extra work-groups of an att
 constexpr int64_t kRowsStart = 14;
 constexpr int64_t kRowsChunkCost = 84;       // chunk prefill: the rows kernel up to this cost
 
+int64_t rows_cost(const RowsPlan& p, int Hkv) {
+  const int64_t rounds = (int64_t(Hkv) * p.n_rt * p.parts + vico::kNumCUs - 1) / vico::kNumCUs;
+  return rounds * (kRowsStart + p.part_blocks * (p.row_blocks == 2 ? 11 : 10) / 10) + (p.parts > 1 ? kRowsStart : 0);
+}
+
 RowsPlan plan_rows(int64_t NR, int Hkv, int64_t keys, int max_parts, int exact_parts) {
   RowsPlan best{};
   const int64_t blocks = (keys + vico::kRowsBlock - 1) / vico::kRowsBlock;
@@ -209,9 +214,8 @@ RowsPlan plan_rows(int64_t NR, int Hkv, int64_t keys, int max_parts, int exact_p
     const int64_t base = int64_t(Hkv) * p.n_rt;
     p.parts = exact_parts > 0 ? exact_parts
                               : (int)std::max<int64_t>(1, std::min<int64_t>(max_parts, vico::kNumCUs / base));
-    const int64_t rounds = (base * p.parts + vico::kNumCUs - 1) / vico::kNumCUs;
     p.part_blocks = (blocks + p.parts - 1) / p.parts;
-    p.cost = rounds * (kRowsStart + p.part_blocks * (rb == 2 ? 11 : 10) / 10) + (p.parts > 1 ? kRowsStart : 0);
+    p.cost = rows_cost(p, Hkv);
     if (rb == 1 || p.cost < best.cost) best = p;
   }
   return best;
@@ -228,6 +232,51 @@ RowsPlan plan_rows(int64_t NR, int Hkv, int64_t keys, int max_parts, int exact_p
 bool chunk_takes_rows(const Shape& sh, int num_splits, RowsPlan* rp) {
   *rp = plan_rows(int64_t(sh.Hq / sh.Hkv) * sh.C, sh.Hkv, int64_t(sh.S) + sh.Wv + sh.C, sh.splits, 0);
   return num_splits == 0 && rp->cost <= kRowsChunkCost;
+}
+
+// Cost of the 256-row gathered kernel for `keys` keys, in the unit of
+// RowsPlan::cost (a block of the rows kernel at full load, 0.28 us at head_dim
+// 128, 0.11 us at 64): rounds * (start + 64-key tiles per part), plus the merge,
+// whose partials are written and read (0.37 us a MB).  Measured a tile: 2.0 us
+// at head_dim 128 (7B heads, 2048 query tokens, 67.8 us for 33 tiles), 1.28 at 64.
+int64_t gather_cost(const GatherShape& sh, int64_t keys) {
+  const bool d128 = sh.D == 128;
+  const int64_t tiles = (keys + vico::kKeyTile - 1) / vico::kKeyTile, groups = int64_t(sh.Hkv) * sh.n_rt * sh.parts;
+  const int64_t rounds = (groups + vico::kNumCUs - 1) / vico::kNumCUs, per_part = (tiles + sh.parts - 1) / sh.parts;
+  const int64_t merge = sh.parts > 1 ? kRowsStart + sh.ws_bytes * (d128 ? 13 : 35) / 10000000 : 0;
+  return rounds * (18 + per_part * (d128 ? 72 : 120) / 10) + merge;
+}
+
+// Whether a gathered call takes the rows kernel.  It does with tables of up to
+// 64 entries where its work-groups' key ranges are short: each row tile streams
+// the keys for itself, while the 256-row kernel reads them once for all rows.
+// Measured with 32 chunks (20.5k keys, 7B heads), us per call, rows against
+// 256-row kernel: 7 rows 16.6 / 22.6, 56 rows 20.9 / 26.5, 112 rows (40 blocks a
+// part) 26.6 / 28.6, 168 rows (64 blocks) 34.0 / 32.9; 3B heads, 384 rows (64
+// blocks, two tiles of the 256-row kernel) 30.1 / 33.9.
+//
+// More work-groups than CUs walk those ranges in rounds, which the 256-row
+// kernel's larger tiles save: then the two costs decide.  7B heads, us, rows
+// against 256-row kernel, no store: 384 query tokens (2 rounds) 18.5 / 22.6, 768
+// (3 rounds) 33 / 33, 1024 (4 rounds) 49 / 37, 2048 (7 rounds) 128 / 68; 512
+// stored keys: 512 tokens 28 / 33, 768 45 / 42, 1024 65 / 46; 3B heads, 1024
+// tokens (2 rounds) no store 28 / 30, 512 keys 36 / 34.  Without a hint the store's
+// keys are not known: the costs then have to say the same with none of the
+// store and with all of it once (7B heads, 20.5k keys, no hint: 384 tokens 345 /
+// 645, 512 345 / 340, 1024 682 / 352).
+bool gather_takes_rows(const GatherShape& sh, int64_t hint, int num_splits, RowsPlan* rp) {
+  const int64_t rows = int64_t(sh.Hq / sh.Hkv) * sh.Lq, known = int64_t(sh.S) + std::min<int64_t>(hint, kMaxKeys) + sh.T;
+  *rp = plan_rows(rows, sh.Hkv, known, sh.parts, num_splits > 0 ? sh.parts : 0);
+  if (sh.n_segs > vico::kRowsMaxSegments) return false;
+  if (rp->n_rt > 1 && rp->part_blocks > (rows > 256 ? 72 : 56)) return false;
+  if (rp->n_rt == 1 || int64_t(sh.Hkv) * rp->n_rt * rp->parts <= vico::kNumCUs) return true;
+  if (rp->cost > gather_cost(sh, known)) return false;
+  if (hint > 0 || sh.n_segs == 0) return true;
+  // the same tiles and parts over all of the store.  Over such ranges the time goes with the work-groups, not
+  // with whole rounds, and a block costs the same with one and two row blocks.
+  const int64_t all = known + sh.cap, blocks = (all + vico::kRowsBlock - 1) / vico::kRowsBlock;
+  const int64_t each = kRowsStart + (blocks + rp->parts - 1) / rp->parts;
+  return int64_t(sh.Hkv) * rp->n_rt * rp->parts * each <= gather_cost(sh, all) * vico::kNumCUs;
 }
 
 bool aligned_to(const void* p, uintptr_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; }
@@ -548,6 +597,21 @@ int vico_gather_plan(int32_t q_len, int32_t tail_len, int32_t sink_len, int32_t 
   return VICO_OK;
 }
 
+int vico_gather_route(int32_t q_len, int32_t tail_len, int32_t sink_len, int32_t store_slots, int32_t num_segments,
+                      int64_t keys_hint, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
+                      int32_t num_splits, int32_t* route_out) {
+  GatherShape sh;
+  const int st = check_gather_shape(q_len, tail_len, sink_len, store_slots, num_segments, keys_hint, num_q_heads,
+                                    num_kv_heads, head_dim, num_splits, &sh);
+  if (st != VICO_OK) return st;
+  RowsPlan rp;
+  const bool rows = q_len > 0 && gather_takes_rows(sh, keys_hint, num_splits, &rp);
+  route_out[0] = rows ? vico::kRouteRows : vico::kRouteGather;
+  route_out[1] = rows ? rp.parts : sh.parts;
+  route_out[2] = sh.Hkv * route_out[1] * (rows ? rp.n_rt : sh.n_rt);
+  return VICO_OK;
+}
+
 int vico_gather_attn(const void* q, int32_t q_len, const void* tail_k, const void* tail_v, int32_t tail_len,
                      const void* sink_k, const void* sink_v, int32_t sink_len, const void* store_k,
                      const void* store_v, int32_t store_slots, const int64_t* seg_start, const int32_t* seg_len,
@@ -628,18 +692,9 @@ int vico::gather_attn_entry(const void* q, int32_t q_len, const void* tail_k, co
   a.out_f32 = out_dtype == VICO_DTYPE_F32;
   const double scale = softmax_scale > 0.f ? double(softmax_scale) : 1.0 / sqrt(double(head_dim));
   a.scale_log2 = (float)(scale * 1.4426950408889634);
-  // The rows kernel takes tables of up to 64 entries where its work-groups'
-  // key ranges are short: each row tile streams the keys for itself, while
-  // the 256-row kernel reads them once for all rows.  Measured with 32 chunks
-  // (20.5k keys, 7B heads), us per call, rows against 256-row kernel: 7 rows
-  // 16.6 / 22.6, 56 rows 20.9 / 26.5, 112 rows (40 blocks a part) 26.6 / 28.6,
-  // 168 rows (64 blocks) 34.0 / 32.9; 3B heads, 384 rows (64 blocks, two tiles
-  // of the 256-row kernel) 30.1 / 33.9.
   hipError_t e;
-  const int64_t rows = int64_t(sh.Hq / sh.Hkv) * sh.Lq;
-  const RowsPlan rp = plan_rows(rows, sh.Hkv, int64_t(sh.S) + std::min<int64_t>(keys_hint, kMaxKeys) + sh.T, sh.parts,
-                                num_splits > 0 ? sh.parts : 0);
-  if (sh.n_segs <= vico::kRowsMaxSegments && (rp.n_rt == 1 || rp.part_blocks <= (rows > 256 ? 72 : 56))) {
+  RowsPlan rp;
+  if (gather_takes_rows(sh, keys_hint, num_splits, &rp)) {
     vico::RowsArgs r{};
     r.q = a.q; r.tail_k = a.tail_k; r.tail_v = a.tail_v; r.sink_k = a.sink_k; r.sink_v = a.sink_v;
     r.store_k = a.store_k; r.store_v = a.store_v; r.seg_start = a.seg_start; r.seg_len = a.seg_len;

@@ -186,4 +186,7 @@ extern "C" {
 int vico_attn_route(int32_t chunk_len, int32_t sink_len, int32_t ring_slots, int64_t hist_len, int64_t window,
                     int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim, int32_t num_splits, int32_t flags,
                     int32_t* route_out);
+int vico_gather_route(int32_t q_len, int32_t tail_len, int32_t sink_len, int32_t store_slots, int32_t num_segments,
+                      int64_t keys_hint, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
+                      int32_t num_splits, int32_t* route_out);
 }

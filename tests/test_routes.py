@@ -3,8 +3,8 @@ import pytest
 import torch
 
 import paper_2606_19849_amd as vico
-from synth import ChunkShape, make_chunk_inputs
-from tests._route import BALANCED, TILE, chunk_route
+from synth import ChunkShape, QueryShape, make_chunk_inputs, make_query_inputs
+from tests._route import BALANCED, GATHER, ROWS, TILE, chunk_route, gather_route
 
 # one and two whole row tiles of equal length per work-group: the balanced shares hold no part of a row tile
 WHOLE_TILES = [ChunkShape(256, 256, 64, 0, 200, 300, 170, 40), ChunkShape(512, 512, 64, 3, 256, 300, 190, 9),
@@ -34,3 +34,50 @@ def test_balanced_calls_of_whole_row_tiles(case):
     assert dc.parts == 1
     ref, ref_lse, b = oracle_and_bound(inp)
     check_f32(o, ref, b, lse, ref_lse)
+
+
+HEADS = {"7b": (28, 4, 128), "3b": (16, 2, 128), "small": (8, 2, 64), "mha": (32, 32, 128)}
+
+# (segments, keys in them), hint given; per head set the query lengths at which one kernel was measured
+# clearly faster than the other (sink of 64, the tail as long as the query)
+FASTER = [
+    (0, 0, False, {"7b": ([8, 64, 256, 384, 512], [1024, 2048]), "3b": ([8, 256, 768], [2048]),
+                   "small": ([64, 1024, 2048], []), "mha": ([64, 256, 512], [1024, 2048])}),
+    (8, 512, True, {"7b": ([8, 64, 256, 384, 512], [1024, 2048]), "3b": ([8, 256, 512], [1024, 2048]),
+                    "small": ([64, 1024], []), "mha": ([64, 256, 512], [768, 1024, 2048])}),
+    (8, 512, False, {"7b": ([8, 64, 256, 384, 512], [768, 1024, 2048]), "3b": ([8, 256, 512, 768], [1024, 2048]),
+                     "small": ([64, 1024], []), "mha": ([64, 256, 384], [768, 1024, 2048])}),
+    (32, 20480, True, {"7b": ([8, 16], [96, 128, 512, 2048]), "3b": ([8, 48], [192, 512, 2048]), "mha": ([8], [96, 512])}),
+    (32, 20480, False, {"7b": ([8, 64, 256, 384], [768, 1024, 2048]), "3b": ([8, 256, 384], [1024, 2048]),
+                        "small": ([64, 1024], [2048]), "mha": ([64, 384], [512, 768, 1024, 2048])}),
+]
+
+
+@pytest.mark.parametrize("segments,keys,known,by_heads", FASTER)
+def test_gathered_calls_take_the_faster_kernel(segments, keys, known, by_heads):
+    """Long queries, which the rows kernel walks in rounds, stay on the 256-row kernel; without a hint also
+    where only the store's keys make it the faster one."""
+    for name, (rows, gather) in by_heads.items():
+        for q_len in rows + gather:
+            got = gather_route(q_len, q_len, 64, 24000, segments, keys if known else 0, HEADS[name])[0]
+            assert got == (ROWS if q_len in rows else GATHER), (name, q_len)
+
+
+def test_forced_parts_count_as_rounds():
+    # 64 parts of a 32-token query: seven row tiles each would be 1792 work-groups
+    assert gather_route(32, 32, 64, 24000, 32, 2000, HEADS["7b"], 64)[0] == GATHER
+    assert gather_route(1, 64, 64, 24000, 32, 2000, HEADS["7b"], 64)[0] == ROWS
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("q_len,kernel", [(384, ROWS), (500, ROWS), (1000, GATHER)])
+def test_long_queries(q_len, kernel):
+    from tests._gpu import check_f32
+    from tests.test_gpu_retrieval import DeviceQuery
+    qi = make_query_inputs(QueryShape(28, 4, 128, 16, 64, 6, 20, 60, q_len, q_len + 3, 4), seed=77, family="F2")
+    d = DeviceQuery(qi)
+    st, ln = qi.chunk_start[:4], qi.chunk_len[:4]
+    assert gather_route(q_len, q_len + 3, 16, qi.store_len, 4, int(ln.sum()), (28, 4, 128))[0] == kernel
+    o, lse, parts = d.attend(st, ln)
+    ro, rl, b = d.reference(st, ln, parts=max(parts, 8))
+    check_f32(o, ro, b, lse, rl)

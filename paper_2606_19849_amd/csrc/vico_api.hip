@@ -195,7 +195,6 @@ int check_gather_shape(int32_t Lq, int32_t T, int32_t S, int32_t cap, int32_t n_
 // the start (table, Q, first keys, the waves' merge) and the merge launch each
 // take about as long as 14 blocks.
 struct RowsPlan { int row_blocks, n_rt, parts; int64_t part_blocks, cost; };
-constexpr int kAppendGroups = 32;            // most extra work-groups of an attention launch that append
 constexpr int64_t kRowsStart = 14;
 constexpr int64_t kRowsChunkCost = 84;       // chunk prefill: the rows kernel up to this cost
 
@@ -279,6 +278,25 @@ bool gather_takes_rows(const GatherShape& sh, int64_t hint, int num_splits, Rows
   return int64_t(sh.Hkv) * rp->n_rt * rp->parts * each <= gather_cost(sh, all) * vico::kNumCUs;
 }
 
+// Whether the append may run beside the attention: the ring has room for window
+// and chunk, so the slots it writes are outside the window.
+bool appends_beside(const Shape& sh, int flags) {
+  return (flags & VICO_ATTN_APPEND) != 0 && int64_t(sh.Wv) + sh.C <= sh.R;
+}
+
+// Extra work-groups of an unsplit attention launch of `work` work-groups that
+// copy the chunk into the ring, 512 16-byte units each at least.  Up to 32 while
+// the last round leaves CUs idle for them (a CU copies about 57 GB/s).  Behind a
+// full round they run alone, so as many as the copy has work for: 8.4 MB after
+// 512 work-groups (32 heads, 512 tokens) 24.0 us a call without the copy, 31.0
+// with 32 groups, 24.0 with 256; 2048 tokens (34 MB) 91 / 121 / 89.
+int append_groups(const Shape& sh, int64_t work) {
+  constexpr int kBeside = 32;
+  const int64_t units = int64_t(2) * sh.C * sh.Hkv * sh.D / 8, most = (units + 511) / 512;
+  const int64_t idle = (vico::kNumCUs - work % vico::kNumCUs) % vico::kNumCUs, beside = std::min<int64_t>(most, kBeside);
+  return (int)(beside <= idle ? beside : std::min<int64_t>(most, vico::kNumCUs));
+}
+
 bool aligned_to(const void* p, uintptr_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; }
 
 int hip_fail(hipError_t e) {
@@ -342,6 +360,7 @@ int vico_attn_route(int32_t chunk_len, int32_t sink_len, int32_t ring_slots, int
                                   head_dim, num_splits, flags, &sh);
   if (st != VICO_OK) return st;
   RowsPlan rp;
+  const bool beside = appends_beside(sh, flags);
   if (chunk_len > 0 && chunk_takes_rows(sh, num_splits, &rp)) {
     route_out[0] = vico::kRouteRows;
     route_out[1] = rp.parts;
@@ -351,6 +370,7 @@ int vico_attn_route(int32_t chunk_len, int32_t sink_len, int32_t ring_slots, int
     route_out[1] = sh.splits;
     route_out[2] = sh.grid;
   }
+  route_out[3] = beside && route_out[1] == 1 ? append_groups(sh, route_out[2]) : 0;
   return VICO_OK;
 }
 
@@ -456,8 +476,7 @@ int vico_chunk_prefill_attn_ex(const void* q, const void* k_chunk, const void* v
   // window: extra work-groups of the attention launch copy the chunk while the
   // others attend (77-token chunk 10.6 -> 7.3 us a call, 7B chunk 461 -> 457).
   // Otherwise the copy is a launch of its own after every read of the window.
-  const bool beside = append && int64_t(sh.Wv) + chunk_len <= ring_slots;
-  const int app_groups = beside ? (int)std::min<int64_t>((cb / 8 + 511) / 512, kAppendGroups) : 0;
+  const bool beside = appends_beside(sh, flags);
   const double scale = softmax_scale > 0.f ? double(softmax_scale) : 1.0 / sqrt(double(head_dim));
   a.scale_log2 = (float)(scale * 1.4426950408889634);
   RowsPlan rp;
@@ -476,9 +495,9 @@ int vico_chunk_prefill_attn_ex(const void* q, const void* k_chunk, const void* v
     r.stage = rp.n_rt > 1;
     r.out_f32 = a.out_f32; r.bidir = a.bidir; r.scale_log2 = a.scale_log2;
     const vico::AppendArgs ap{a.kc, a.vc, a.app_rk, a.app_rv, a.C, a.R, a.app_p0, a.Hkv * a.D};
-    if (rp.parts == 1 && app_groups > 0) {
+    if (rp.parts == 1 && beside) {
       r.app = ap;
-      r.app_blocks = app_groups;
+      r.app_blocks = append_groups(sh, int64_t(sh.Hkv) * rp.n_rt);
     }
     hipError_t e = vico::launch_rows(r, (hipStream_t)stream);
     if (e == hipSuccess && rp.parts > 1) {
@@ -489,7 +508,7 @@ int vico_chunk_prefill_attn_ex(const void* q, const void* k_chunk, const void* v
     }
     return e == hipSuccess ? VICO_OK : hip_fail(e);
   }
-  if (sh.splits == 1) a.app_blocks = app_groups;
+  if (sh.splits == 1 && beside) a.app_blocks = append_groups(sh, sh.grid);
   const hipError_t e = vico::launch_attention(a, sh.grid, (hipStream_t)stream);
   return e == hipSuccess ? VICO_OK : hip_fail(e);
 }
@@ -609,6 +628,7 @@ int vico_gather_route(int32_t q_len, int32_t tail_len, int32_t sink_len, int32_t
   route_out[0] = rows ? vico::kRouteRows : vico::kRouteGather;
   route_out[1] = rows ? rp.parts : sh.parts;
   route_out[2] = sh.Hkv * route_out[1] * (rows ? rp.n_rt : sh.n_rt);
+  route_out[3] = 0;
   return VICO_OK;
 }
 

@@ -178,7 +178,8 @@ hipError_t launch_topk(const float* scores, int N, int k, float min_score, const
 // ---- which kernel a call of these arguments runs, by the same code that the
 // call itself runs; nothing is launched.  For tests: not part of the public
 // interface.  route_out: {kernel, key-range parts (1: no merge launch),
-// attention work-groups}.
+// attention work-groups, further ones that do the append (0: not beside the
+// attention)}.
 namespace vico {
 enum Route { kRouteTile = 0, kRouteBalanced = 1, kRouteRows = 2, kRouteGather = 3 };
 }

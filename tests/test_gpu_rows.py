@@ -134,7 +134,9 @@ def test_tile_kernel_short_ranges(case, flags):
     # ring with room for window and chunk (the copy rides on the attention launch), exactly and with a wrap
     (8, 2, 128, 16, 400, 777, 300, 77), (8, 2, 128, 0, 377, 5000, 300, 77), (8, 1, 64, 3, 2000, 3999, 1500, 300),
     # one slot short of it (the copy is a launch of its own)
-    (8, 2, 128, 16, 376, 777, 300, 77)])
+    (8, 2, 128, 16, 376, 777, 300, 77),
+    # 256 work-groups, and twice 256: a wide copy behind the full rounds
+    (32, 32, 128, 3, 400, 900, 100, 256), (32, 32, 64, 0, 700, 1500, 10, 512)])
 @pytest.mark.parametrize("splits", [0, 1, 2])
 def test_append_beside_the_attention(shape, splits):
     """One call with the append equals the attention and then vico_kv_append, bit for bit, ring included."""

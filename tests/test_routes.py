@@ -18,7 +18,7 @@ def test_balanced_shares_of_whole_row_tiles_take_the_plain_schedule(sh):
     for flags in (0, vico.VICO_ATTN_BIDIRECTIONAL):
         parts, wb = vico.vico_attn_plan(sh.chunk_len, sh.sink_len, sh.ring_slots, sh.hist_len, sh.window, sh.num_q_heads,
                                         sh.num_kv_heads, sh.head_dim, vico.VICO_SPLIT_BALANCED, flags)
-        kernel, _, groups = chunk_route(sh, vico.VICO_SPLIT_BALANCED, flags)
+        kernel, _, groups, _ = chunk_route(sh, vico.VICO_SPLIT_BALANCED, flags)
         assert (kernel == BALANCED) == (parts > 1) == (wb > 0)
         if parts == 1:
             assert kernel == TILE and groups >= 256
@@ -81,3 +81,16 @@ def test_long_queries(q_len, kernel):
     o, lse, parts = d.attend(st, ln)
     ro, rl, b = d.reference(st, ln, parts=max(parts, 8))
     check_f32(o, ro, b, lse, rl)
+
+
+@pytest.mark.parametrize("sh,splits,groups", [
+    (ChunkShape(28, 4, 128, 64, 18432, 9 * 18432, 16384, 2048), 0, 32),       # 224 work-groups: beside, on idle CUs
+    (ChunkShape(16, 2, 128, 64, 512, 4001, 307, 77), 0, 10),                  # all that the copy has work for
+    (ChunkShape(32, 32, 128, 64, 640, 2000, 0, 512), 0, 256),                 # two full rounds: the copy runs after them
+    (ChunkShape(32, 32, 128, 64, 640, 2000, 256, 256), 0, 256),
+    (ChunkShape(32, 4, 128, 64, 4096, 9000, 1024, 2048), 1, 256),             # the tile kernel, one full round
+    (ChunkShape(16, 2, 128, 64, 576, 2000, 320, 256), 0, 32),                 # a small copy after a full round
+    (ChunkShape(16, 2, 128, 64, 575, 2000, 320, 256), 0, 0)])                 # no room beside the window
+def test_append_groups_beside_the_attention(sh, splits, groups):
+    assert chunk_route(sh, splits, vico.VICO_ATTN_APPEND)[3] == groups
+    assert chunk_route(sh, splits)[3] == 0

@@ -1,6 +1,8 @@
 """The C++ calls of the binding against its ctypes path: what the first takes
 gives the same results, what it does not take is accepted or rejected by the
 second in its own words."""
+import warnings
+
 import numpy as np
 import pytest
 import torch
@@ -28,6 +30,25 @@ def test_host_tensors_go_to_the_general_path():
         vico.vico_token_mean(bf(3, 64), torch.zeros(64))
     with pytest.raises(ValueError, match="expected a contiguous"):
         vico.vico_kv_append(bf(4, 1, 64), bf(4, 1, 64), bf(8, 1, 64), bf(8, 1, 64), 0)
+
+
+def test_without_the_cpp_calls_the_ctypes_path_runs(monkeypatch, tmp_path):
+    """A tree with libvico alone still works: a warning once, then the general path in its own words."""
+    monkeypatch.setattr(binding, "_calls", None)
+    monkeypatch.setattr(binding, "CALL_PATH", str(tmp_path / "_vico_call.so"))
+    x, out = torch.zeros(3, 64, dtype=torch.bfloat16), torch.zeros(64)
+    with pytest.warns(RuntimeWarning, match="build it"), pytest.raises(ValueError, match="expected a contiguous"):
+        vico.vico_token_mean(x, out)
+    with warnings.catch_warnings(), pytest.raises(ValueError, match="expected a contiguous"):
+        warnings.simplefilter("error")
+        vico.vico_token_mean(x, out)
+    # as vico_kv_append, up to the library: an empty chunk is accepted there
+    seen = []
+    monkeypatch.setattr(binding, "_dev_bf16", lambda *a: None)
+    monkeypatch.setattr(binding, "_stream", lambda s: seen.append(s) or None)
+    empty = torch.zeros(0, 1, 64, dtype=torch.bfloat16)
+    vico.vico_kv_append(empty, empty, torch.zeros(8, 1, 64), torch.zeros(8, 1, 64), 0)
+    assert seen == [None]
 
 
 @pytest.mark.gpu

@@ -42,6 +42,11 @@ __device__ __forceinline__ float pair_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// The log2-sum-exp that a key-range part leaves for the merge: NaN where the
+// part's sum is (a NaN or infinite logit), or the merge would take the part for
+// one that saw no key and drop it.
+__device__ __forceinline__ float part_lse(float sum, float lse2) { return sum == sum ? lse2 : sum; }
+
 // Raw buffer resource over `bytes` bytes (stride 0, 32-bit data format).
 // Reads at offsets >= bytes return zero.
 __device__ __forceinline__ rsrc_t make_rsrc(const void* p, int bytes) {
@@ -246,11 +251,12 @@ struct WaveTile {
   }
 
   // Row totals over the two lanes of a row: 1/l (0 for an empty row) and the
-  // log2-sum-exp (-inf for an empty row).
-  __device__ __forceinline__ void finish(float& inv, float& lse2) const {
+  // log2-sum-exp (-inf for an empty row), also as a part leaves it.
+  __device__ __forceinline__ void finish(float& inv, float& lse2, float& part_lse2) const {
     const float l_tot = pair_sum(l_run);
     inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
     lse2 = l_tot > 0.f ? m_run + __log2f(l_tot) : -INFINITY;
+    part_lse2 = part_lse(l_tot, lse2);
   }
 };
 

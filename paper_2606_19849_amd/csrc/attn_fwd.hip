@@ -411,7 +411,7 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs& a, int n_rt, int g
     if (!partial) {
       if (a.lse) a.lse[(int64_t)hd * C + row] = lse2 * kLn2;
     } else {
-      a.ws_lse[((int64_t)part * a.Hq + hd) * C + row] = lse2;
+      a.ws_lse[((int64_t)part * a.Hq + hd) * C + row] = part_lse(l_tot, lse2);
       // a row tile that ends in this segment uses no later parts
       if (t_hi == n_tiles)
         for (int p2 = part + 1; p2 < n_parts; ++p2) a.ws_lse[((int64_t)p2 * a.Hq + hd) * C + row] = -INFINITY;

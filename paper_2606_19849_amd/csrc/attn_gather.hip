@@ -309,8 +309,8 @@ __global__ __launch_bounds__(kGatherThreads, 1) void attn_gather_kernel(GatherAr
   }
 
   if (!wave_active || my_row >= NR) return;
-  float inv, lse2;
-  wt.finish(inv, lse2);
+  float inv, lse2, part_lse2;
+  wt.finish(inv, lse2, part_lse2);
   const int64_t orow = (int64_t)my_tok * a.Hq + my_head;
   if (a.parts == 1) {
     if (a.out_f32) {
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(kGatherThreads, 1) void attn_gather_kernel(GatherAr
       for (int q4 = 0; q4 < 4; ++q4)
         *(f32x4*)(op + db * 32 + q4 * 8) = f32x4{o[db][q4 * 4] * inv, o[db][q4 * 4 + 1] * inv,
                                                  o[db][q4 * 4 + 2] * inv, o[db][q4 * 4 + 3] * inv};
-    if (hh == 0) a.ws_lse[pr] = lse2;
+    if (hh == 0) a.ws_lse[pr] = part_lse2;
   }
 }
 

@@ -353,7 +353,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_rows_kernel(RowsArgs a) {
     if (a.parts > 1) {
       const int64_t prow = ((int64_t)part * a.Hq + h) * a.Lq + t;      // the merge kernel's layout
       *(f32x4*)(a.ws_o + prow * D + dq * 4) = acc;
-      if (dq == 0) a.ws_lse[prow] = lse2;
+      if (dq == 0) a.ws_lse[prow] = part_lse(l, lse2);
       continue;
     }
     const int64_t oo = ((int64_t)t * a.Hq + h) * D + dq * 4;

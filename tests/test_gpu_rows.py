@@ -172,3 +172,31 @@ def test_later_tokens_stay_out_of_earlier_rows(shape, splits, poison):
     apart = (first + last_of_wave) // 64 < (first + sh.chunk_len - 1) // 64
     assert apart.any()
     assert np.array_equal(o[apart], clean[apart]) and np.array_equal(lse[:, apart], clean_lse[:, apart])
+
+
+@pytest.mark.parametrize("poison", [float("nan"), float("inf")])
+@pytest.mark.parametrize("splits", [0, 1, 3, 16, vico.VICO_SPLIT_BALANCED])
+@pytest.mark.parametrize("shape", [(4, 2, 128, 5, 1200, 2000, 1150, 40), (8, 2, 128, 64, 4096, 4596, 4000, 600),
+                                   (8, 2, 64, 0, 4096, 4500, 4000, 64)])
+def test_nan_logits_stay_in_a_split_result(shape, splits, poison):
+    """A NaN or infinite logit makes its row NaN, however the keys are split: the part that holds it is not
+    taken for an empty one.  The key is the oldest of the window, which every row sees."""
+    dc = DeviceChunk(make_chunk_inputs(ChunkShape(*shape), seed=432, family="F2"))
+    sh = dc.inp.shape
+    dc.rk[(sh.hist_len - sh.visible_window) % sh.ring_slots] = poison
+    o, lse = dc.attention(num_splits=splits)
+    assert np.isnan(o).all()
+
+
+@pytest.mark.parametrize("splits", [0, 1, 5, 24])
+@pytest.mark.parametrize("pad", [0, 60])
+@pytest.mark.parametrize("q_len", [1, 20])
+def test_nan_logits_stay_in_a_split_gathered_result(splits, pad, q_len):
+    """The same for the gathered call, on the rows kernel and (65 table entries) on the 256-row kernel."""
+    qi = make_query_inputs(QueryShape(8, 2, 128, 19, 64, 12, 100, 300, q_len, q_len, 5), seed=433, family="F2")
+    d = DeviceQuery(qi)
+    st = np.concatenate([qi.chunk_start[:5], np.zeros(pad, np.int64)])
+    ln = np.concatenate([qi.chunk_len[:5], np.zeros(pad, np.int32)])
+    d.gk[int(st[2])] = float("nan")
+    o, lse, parts = d.attend(st, ln, num_splits=splits)
+    assert np.isnan(o).all()

@@ -262,14 +262,16 @@ int64_t gather_cost(const GatherShape& sh, int64_t keys) {
 // tokens (2 rounds) no store 28 / 30, 512 keys 36 / 34.  Without a hint the store's
 // keys are not known: the costs then have to say the same with none of the
 // store and with all of it once (7B heads, 20.5k keys, no hint: 384 tokens 345 /
-// 645, 512 345 / 340, 1024 682 / 352).
+// 645, 512 345 / 340, 1024 682 / 352).  Parts that the caller chose may be empty
+// ones, which the costs do not describe: beyond one round they stay on the
+// 256-row kernel (32 heads, 64 tokens, 256 keys in 64 parts 101 / 62).
 bool gather_takes_rows(const GatherShape& sh, int64_t hint, int num_splits, RowsPlan* rp) {
   const int64_t rows = int64_t(sh.Hq / sh.Hkv) * sh.Lq, known = int64_t(sh.S) + std::min<int64_t>(hint, kMaxKeys) + sh.T;
   *rp = plan_rows(rows, sh.Hkv, known, sh.parts, num_splits > 0 ? sh.parts : 0);
   if (sh.n_segs > vico::kRowsMaxSegments) return false;
   if (rp->n_rt > 1 && rp->part_blocks > (rows > 256 ? 72 : 56)) return false;
   if (rp->n_rt == 1 || int64_t(sh.Hkv) * rp->n_rt * rp->parts <= vico::kNumCUs) return true;
-  if (rp->cost > gather_cost(sh, known)) return false;
+  if (num_splits > 0 || rp->cost > gather_cost(sh, known)) return false;
   if (hint > 0 || sh.n_segs == 0) return true;
   // the same tiles and parts over all of the store.  Over such ranges the time goes with the work-groups, not
   // with whole rounds, and a block costs the same with one and two row blocks.

@@ -64,6 +64,9 @@ def test_gathered_calls_take_the_faster_kernel(segments, keys, known, by_heads):
 
 
 def test_forced_parts_count_as_rounds():
+    for name, keys, parts in (("mha", 0, 64), ("mha", 256, 16), ("mha", 4096, 16), ("small", 4096, 64), ("small", 10000, 64)):
+        assert gather_route(64, 300, 64, 24000, 8, keys, HEADS[name], parts)[0] == GATHER, (name, parts)
+    assert gather_route(64, 300, 64, 24000, 8, 4096, HEADS["small"], 16)[0] == ROWS       # one round
     # 64 parts of a 32-token query: seven row tiles each would be 1792 work-groups
     assert gather_route(32, 32, 64, 24000, 32, 2000, HEADS["7b"], 64)[0] == GATHER
     assert gather_route(1, 64, 64, 24000, 32, 2000, HEADS["7b"], 64)[0] == ROWS

@@ -136,9 +136,11 @@ int vico_chunk_prefill_attn(const void* q, const void* k_chunk, const void* v_ch
  * chunk[0 .. chunk_len) instead of chunk[0 .. i].  VICO_ATTN_APPEND: after
  * attending, the call also does what vico_kv_append(k_chunk, v_chunk, ...,
  * hist_len) would (the ring of Sec. 3 advances by the chunk), after every
- * read of the window: the split-merge kernel copies the chunk alongside the
- * merge, so a split call saves a launch; without a split the copy is its own
- * launch.  It needs ring_k/ring_v, chunk_len <= ring_slots, and chunk buffers
+ * read of a ring slot that it writes: the split-merge kernel copies the chunk
+ * alongside the merge; without a split, work-groups of the attention launch
+ * copy it where the ring has room for window and chunk (Wv + chunk_len <=
+ * ring_slots: none of the written slots is read then), and the copy is a launch
+ * of its own where it has not.  It needs ring_k/ring_v, chunk_len <= ring_slots, and chunk buffers
  * that do not overlap the ring (as vico_kv_append).  Other bits are invalid.
  * Use vico_attn_plan_ex with the same flags for the workspace size.
  *
@@ -168,10 +170,12 @@ int vico_chunk_prefill_attn_ex(const void* q, const void* k_chunk, const void* v
 int64_t vico_acn_window(const int64_t* chunk_starts, int32_t num_chunks, int32_t t, int32_t acn);
 
 /*
- * vico_attn_plan -- how vico_chunk_prefill_attn will run for these arguments.
+ * vico_attn_plan -- what vico_chunk_prefill_attn asks for with these arguments.
  * Host-only; validates the shape arguments exactly as the attention call does.
- *   *num_splits_out      partial results merged per row (1 = no merge)
- *   *workspace_bytes_out device scratch the call needs (0 when not split)
+ *   *num_splits_out      most partial results merged per row (1 = no merge); with
+ *                        num_splits = 0 a short call may use fewer
+ *   *workspace_bytes_out device scratch for that many, which the call requires
+ *                        (0 when not split)
  * Either output pointer may be NULL.
  */
 int vico_attn_plan(int32_t chunk_len, int32_t sink_len, int32_t ring_slots, int64_t hist_len,
@@ -264,8 +268,9 @@ int vico_topk_chunks(const float* scores, int32_t num_chunks, int32_t top_k, flo
  *   store_k,store_v[store_slots][num_kv_heads][head_dim] bf16, device
  *   seg_start      [num_segments] int64, device (8-byte aligned)
  *   seg_len        [num_segments] int32, device (4-byte aligned)
- *   keys_hint      expected total segment length; only sets how the key range
- *                  is split over work-groups (any value gives the same result)
+ *   keys_hint      expected total segment length (0: not known); only sets how
+ *                  the work is split and which kernel runs (any value gives the
+ *                  same result up to rounding)
  *   out, out_dtype, lse_out, softmax_scale: as for vico_chunk_prefill_attn
  *                  ([q_len][num_q_heads][head_dim], [num_q_heads][q_len])
  *   num_splits     0: library's choice; n > 0: key range in n parts (<= 64)
@@ -285,8 +290,10 @@ int vico_gather_attn(const void* q, int32_t q_len, const void* tail_k, const voi
                      int32_t num_splits, void* workspace, int64_t workspace_bytes, void* stream);
 
 /*
- * vico_gather_plan -- key-range parts and workspace of vico_gather_attn for
- * these arguments (host-only; validates them as the call does).
+ * vico_gather_plan -- most key-range parts that vico_gather_attn takes with
+ * these arguments (with num_splits = 0 it may take fewer) and the workspace for
+ * that many, which the call requires (host-only; validates the arguments as the
+ * call does).
  */
 int vico_gather_plan(int32_t q_len, int32_t tail_len, int32_t sink_len, int32_t store_slots,
                      int32_t num_segments, int64_t keys_hint, int32_t num_q_heads, int32_t num_kv_heads,

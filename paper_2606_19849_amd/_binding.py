@@ -165,7 +165,7 @@ def vico_kv_append(k_chunk, v_chunk, ring_k, ring_v, hist_len: int, stream=None)
 
 def vico_attn_plan(chunk_len, sink_len, ring_slots, hist_len, window, num_q_heads, num_kv_heads, head_dim,
                    num_splits=0, flags: int = 0):
-    """(splits, workspace_bytes) the attention call will use (vico_attn_plan_ex)."""
+    """(most splits, workspace_bytes) of the attention call (vico_attn_plan_ex)."""
     ns, wb = _i32(0), _i64(0)
     st = load_library().vico_attn_plan_ex(chunk_len, sink_len, ring_slots, int(hist_len), int(window),
                                           num_q_heads, num_kv_heads, head_dim, num_splits, int(flags),
@@ -287,7 +287,7 @@ def vico_topk_chunks(scores, top_k: int, out_chunks, out_scores, out_count, min_
 
 def vico_gather_plan(q_len, tail_len, sink_len, store_slots, num_segments, keys_hint, num_q_heads, num_kv_heads,
                      head_dim, num_splits=0):
-    """(parts, workspace_bytes) of vico_gather_attn for these arguments."""
+    """(most parts, workspace_bytes) of vico_gather_attn for these arguments."""
     ns, wb = _i32(0), _i64(0)
     st = load_library().vico_gather_plan(q_len, tail_len, sink_len, store_slots, num_segments, int(keys_hint),
                                          num_q_heads, num_kv_heads, head_dim, num_splits,

@@ -233,6 +233,22 @@ bool chunk_takes_rows(const Shape& sh, int num_splits, RowsPlan* rp) {
   return num_splits == 0 && rp->cost <= kRowsChunkCost;
 }
 
+// Whether the rows kernel brings K through LDS.  A chunk: as soon as two row
+// tiles read the same keys; us per call, direct and staged, 3B heads, 77 tokens
+// over 307 keys 8.2 / 7.7, 256 over 512 11.8 / 10.9, 512 over 1024 20.9 / 19.1; small
+// heads, 300 tokens over 512 8.1 / 6.5; 7B heads, 163 tokens over 676 14.7 / 14.1.
+bool chunk_stages(const RowsPlan& rp) { return rp.n_rt > 1; }
+
+// A gathered call: a store is mostly read from HBM, and few row tiles wait for
+// that alone.  us a layer of a query pass (the retrieval's share is 0.4), direct
+// and staged, 32 chunks (20.5k keys) of 128-dim heads: 2 row tiles 21.4 / 22.8, 4
+// tiles 27.6 / 27.9, 5 tiles 32.1 / 31.4, 12 tiles 33.8 / 32.3; 8 short chunks (one
+// block a wave), 7 tiles 11.8 / 11.9.  64-dim heads: 2 tiles 11.4 / 11.0, 6 tiles
+// 14.4 / 12.6.
+bool gather_stages(const GatherShape& sh, const RowsPlan& rp) {
+  return rp.n_rt > 1 && (sh.D == 64 || (rp.n_rt >= 5 && rp.part_blocks > 8));
+}
+
 // Cost of the 256-row gathered kernel for `keys` keys, in the unit of
 // RowsPlan::cost (a block of the rows kernel at full load, 0.28 us at head_dim
 // 128, 0.11 us at 64): rounds * (start + 64-key tiles per part), plus the merge,
@@ -367,10 +383,12 @@ int vico_attn_route(int32_t chunk_len, int32_t sink_len, int32_t ring_slots, int
     route_out[0] = vico::kRouteRows;
     route_out[1] = rp.parts;
     route_out[2] = sh.Hkv * rp.n_rt * rp.parts;
+    route_out[4] = chunk_stages(rp);
   } else {
     route_out[0] = sh.balanced ? vico::kRouteBalanced : vico::kRouteTile;
     route_out[1] = sh.splits;
     route_out[2] = sh.grid;
+    route_out[4] = 0;
   }
   route_out[3] = beside && route_out[1] == 1 ? append_groups(sh, route_out[2]) : 0;
   return VICO_OK;
@@ -491,10 +509,7 @@ int vico_chunk_prefill_attn_ex(const void* q, const void* k_chunk, const void* v
     r.seg0 = a.ws; r.len0 = std::min(a.Wv, a.R - a.ws); r.len1 = a.Wv - r.len0;
     r.Hq = a.Hq; r.Hkv = a.Hkv; r.D = a.D;
     r.parts = rp.parts; r.n_rt = rp.n_rt; r.row_blocks = rp.row_blocks;
-    // K through LDS as soon as two row tiles read the same keys: us per call, direct and staged,
-    // 3B heads, 77 tokens over 307 keys 8.2 / 7.7, 256 over 512 11.8 / 10.9, 512 over 1024 20.9 / 19.1;
-    // small heads, 300 tokens over 512 8.1 / 6.5; 7B heads, 163 tokens over 676 14.7 / 14.1
-    r.stage = rp.n_rt > 1;
+    r.stage = chunk_stages(rp);
     r.out_f32 = a.out_f32; r.bidir = a.bidir; r.scale_log2 = a.scale_log2;
     const vico::AppendArgs ap{a.kc, a.vc, a.app_rk, a.app_rv, a.C, a.R, a.app_p0, a.Hkv * a.D};
     if (rp.parts == 1 && beside) {
@@ -631,6 +646,7 @@ int vico_gather_route(int32_t q_len, int32_t tail_len, int32_t sink_len, int32_t
   route_out[1] = rows ? rp.parts : sh.parts;
   route_out[2] = sh.Hkv * route_out[1] * (rows ? rp.n_rt : sh.n_rt);
   route_out[3] = 0;
+  route_out[4] = rows && gather_stages(sh, rp);
   return VICO_OK;
 }
 
@@ -726,12 +742,7 @@ int vico::gather_attn_entry(const void* q, int32_t q_len, const void* tail_k, co
     r.parts = rp.parts; r.n_rt = rp.n_rt; r.row_blocks = rp.row_blocks;
     r.out_f32 = a.out_f32; r.scale_log2 = a.scale_log2;
     if (a.n_segs == 0) r.seg_start = nullptr;
-    // K through LDS: a store is mostly read from HBM, and few row tiles wait for that alone.  us a
-    // layer of a query pass (the retrieval's share is 0.4), direct and staged, 32 chunks (20.5k keys) of
-    // 128-dim heads: 2 row tiles 21.4 / 22.8, 4 tiles 27.6 / 27.9, 5 tiles 32.1 / 31.4, 12 tiles 33.8 /
-    // 32.3; 8 short chunks (one block a wave), 7 tiles 11.8 / 11.9.  64-dim heads: 2 tiles 11.4 / 11.0,
-    // 6 tiles 14.4 / 12.6.
-    r.stage = rp.n_rt > 1 && (a.D == 64 || (rp.n_rt >= 5 && rp.part_blocks > 8));
+    r.stage = gather_stages(sh, rp);
     e = vico::launch_rows(r, (hipStream_t)stream);
     if (e == hipSuccess && r.parts > 1) {
       vico::AttnArgs m{};

@@ -179,7 +179,7 @@ hipError_t launch_topk(const float* scores, int N, int k, float min_score, const
 // call itself runs; nothing is launched.  For tests: not part of the public
 // interface.  route_out: {kernel, key-range parts (1: no merge launch),
 // attention work-groups, further ones that do the append (0: not beside the
-// attention)}.
+// attention), 1 where the rows kernel brings K through LDS}.
 namespace vico {
 enum Route { kRouteTile = 0, kRouteBalanced = 1, kRouteRows = 2, kRouteGather = 3 };
 }

@@ -5,8 +5,9 @@ import torch
 
 import oracle
 import paper_2606_19849_amd as vico
-from synth import f32_to_bf16_bits, ragged_chunk_lengths
+from synth import ChunkShape, f32_to_bf16_bits, ragged_chunk_lengths
 from tests._gpu import bits_of, dev
+from tests._route import ROWS, TILE, chunk_route
 
 pytestmark = pytest.mark.gpu
 
@@ -109,10 +110,11 @@ def test_attention_with_append_equals_attention_then_append(splits, flags):
         H += c
 
 
-@pytest.mark.parametrize("C,splits", [(300, 0), (513, 3), (1024, 0)])
-def test_chunk_call_with_append_replays_as_a_graph(C, splits):
-    """A chunk call with VICO_ATTN_APPEND (attention, the split merge and the
-    ring copy riding on it; a 300-token chunk runs the packed row tiles)
+@pytest.mark.parametrize("C,splits,route", [(300, 0, (ROWS, 2)), (513, 3, (TILE, 3)), (1024, 0, (ROWS, 1)),
+                                            (1024, 2, (TILE, 2)), (300, 1, (TILE, 1))])
+def test_chunk_call_with_append_replays_as_a_graph(C, splits, route):
+    """A chunk call with VICO_ATTN_APPEND (attention, then the split merge with
+    the ring copy riding on it; with one part the copy rides on the attention)
     captured into a HIP graph replays the eager result bit for bit, replay
     after replay, with an eager call of another window on the same buffers in
     between.  The window and the appended slots do not overlap (W + C <= R),
@@ -127,7 +129,9 @@ def test_chunk_call_with_append_replays_as_a_graph(C, splits):
                dev(_rand_bits(rng, (C, Hkv, D))))
     H = 3 * R + 555
     parts, wb = vico.vico_attn_plan(C, S, R, H, W, Hq, Hkv, D, splits, vico.VICO_ATTN_APPEND)
-    assert parts > 1                  # the merge (and the append on it) is part of the graph
+    kernel, merged, _, beside, _ = chunk_route(ChunkShape(Hq, Hkv, D, S, R, H, W, C), splits, vico.VICO_ATTN_APPEND)
+    assert (kernel, merged) == route and merged <= parts       # more than one part: the merge is part of the graph
+    assert (beside > 0) == (merged == 1)
     ws = torch.empty(max(wb, vico.vico_attn_plan(C, S, R, H, W2, Hq, Hkv, D)[1]), dtype=torch.uint8, device="cuda")
     out = torch.empty((C, Hq, D), dtype=torch.float32, device="cuda")
     lse = torch.empty((Hq, C), dtype=torch.float32, device="cuda")

@@ -31,6 +31,7 @@ import paper_2606_19849_amd as vico
 from synth import CONFIGS, QUERY_CONFIGS, QueryShape, make_chunk_inputs, make_query_inputs, make_tokens
 from tests._bounds import Bound, chunk_bound, gather_bound
 from tests._gpu import check_bf16, check_f1, check_f32, dev
+from tests._route import ROWS, gather_route
 from tests._util import ring_from_inputs, to_f64
 
 pytestmark = pytest.mark.gpu
@@ -268,7 +269,10 @@ def test_decode_step_replays_as_a_graph():
     hint = max(int(ln.sum()) for _, ln in tables)
     parts, wb = vico.vico_gather_plan(1, sh.tail_len, sh.sink_len, d.gk.shape[0], 4, hint, sh.num_q_heads,
                                       sh.num_kv_heads, sh.head_dim)
-    assert parts > 1                  # the merge kernel is part of the graph
+    # the rows kernel, and the merge kernel is part of the graph
+    kernel, merged, *_ = gather_route(1, sh.tail_len, sh.sink_len, d.gk.shape[0], 4, hint, (sh.num_q_heads, sh.num_kv_heads,
+                                                                                        sh.head_dim))
+    assert kernel == ROWS and 1 < merged <= parts
     ws = torch.empty(wb, dtype=torch.uint8, device="cuda")
     out = torch.empty((1, sh.num_q_heads, sh.head_dim), dtype=torch.float32, device="cuda")
     lse = torch.empty((sh.num_q_heads, 1), dtype=torch.float32, device="cuda")
@@ -548,7 +552,10 @@ def test_decode_step_full_size(family, query_seed):
     hint = sh.top_k * (sh.chunk_lo + sh.chunk_hi) // 2
     parts, wb = vico.vico_gather_plan(1, sh.tail_len, sh.sink_len, qi.store_len, sh.top_k, hint,
                                       sh.num_q_heads, sh.num_kv_heads, sh.head_dim)
-    assert parts > 1                  # the split and the merge are part of the step
+    # the rows kernel; the split and the merge are part of the step
+    kernel, merged, *_ = gather_route(1, sh.tail_len, sh.sink_len, qi.store_len, sh.top_k, hint,
+                                      (sh.num_q_heads, sh.num_kv_heads, sh.head_dim))
+    assert kernel == ROWS and 1 < merged <= parts
     ws = torch.empty(max(wb, 256), dtype=torch.uint8, device="cuda")
     out = torch.empty((1, sh.num_q_heads, sh.head_dim), dtype=torch.bfloat16, device="cuda")
     lse = torch.empty((sh.num_q_heads, 1), dtype=torch.float32, device="cuda")

@@ -11,6 +11,7 @@ import torch
 import paper_2606_19849_amd as vico
 from synth import ChunkShape, QueryShape, make_chunk_inputs, make_query_inputs
 from tests._gpu import DeviceChunk, check_bf16, check_f32, oracle_and_bound
+from tests._route import GATHER, ROWS, TILE, chunk_route, gather_route
 from tests.test_gpu_retrieval import DeviceQuery
 
 pytestmark = pytest.mark.gpu
@@ -34,11 +35,12 @@ ROWS_CHUNKS = [
 @pytest.mark.parametrize("case", range(len(ROWS_CHUNKS)))
 @pytest.mark.parametrize("flags", [0, vico.VICO_ATTN_BIDIRECTIONAL])
 def test_small_chunks_on_both_kernels(case, flags):
-    """The planner's choice (the rows kernel here) and the tile kernel (a split
+    """The library's choice (the rows kernel here) and the tile kernel (a split
     count given by the caller) against the oracle, fp32 and bf16 results."""
     inp = make_chunk_inputs(ChunkShape(*ROWS_CHUNKS[case]), seed=700 + case, family="F2")
     dc = DeviceChunk(inp)
     for splits in (0, 1, 3):
+        assert chunk_route(inp.shape, splits, flags)[0] == (TILE if splits else ROWS)
         o, lse = dc.attention(torch.float32, num_splits=splits, flags=flags)
         ref, ref_lse, b = oracle_and_bound(inp, parts=max(dc.parts, 8), bidirectional=bool(flags))
         check_f32(o, ref, b, lse, ref_lse)
@@ -69,7 +71,9 @@ def test_gathered_rows(heads, q_len, tail, n_seg):
     pad = 65 - n_seg
     wide = (np.concatenate([st, np.zeros(pad, np.int64)]), np.concatenate([ln, np.zeros(pad, np.int32)]))
     for splits in (0, 3):
-        for table in ((st, ln), wide):
+        for table, kernel in (((st, ln), ROWS), (wide, GATHER)):
+            hint = int(np.maximum(table[1], 0).sum())
+            assert gather_route(q_len, tail, 19, qi.store_len, len(table[0]), hint, heads, splits)[0] == kernel
             o, lse, parts = d.attend(*table, num_splits=splits)
             ro, rl, b = d.reference(lo[keep], (hi - lo)[keep], parts=max(parts, 8))
             check_f32(o, ro, b, lse, rl)
@@ -90,6 +94,8 @@ def test_gathered_rows_through_lds(heads, q_len, n_seg, splits):
     ln = rng.integers(30, 1 + 1800 // n_seg if n_seg < 10 else 71, n_seg).astype(np.int32)
     lo, hi = np.clip(st, 0, qi.store_len), np.clip(st + ln, 0, qi.store_len)
     keep = hi > lo
+    kernel, *_, staged = gather_route(q_len, q_len + 3, 40, qi.store_len, n_seg, 1200, heads, splits)
+    assert kernel == ROWS and staged
     o, lse, parts = d.attend(st, ln, num_splits=splits, hint=1200)
     ro, rl, b = d.reference(lo[keep], (hi - lo)[keep], parts=max(parts, 8))
     check_f32(o, ro, b, lse, rl)

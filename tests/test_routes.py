@@ -18,7 +18,7 @@ def test_balanced_shares_of_whole_row_tiles_take_the_plain_schedule(sh):
     for flags in (0, vico.VICO_ATTN_BIDIRECTIONAL):
         parts, wb = vico.vico_attn_plan(sh.chunk_len, sh.sink_len, sh.ring_slots, sh.hist_len, sh.window, sh.num_q_heads,
                                         sh.num_kv_heads, sh.head_dim, vico.VICO_SPLIT_BALANCED, flags)
-        kernel, _, groups, _ = chunk_route(sh, vico.VICO_SPLIT_BALANCED, flags)
+        kernel, _, groups = chunk_route(sh, vico.VICO_SPLIT_BALANCED, flags)[:3]
         assert (kernel == BALANCED) == (parts > 1) == (wb > 0)
         if parts == 1:
             assert kernel == TILE and groups >= 256

@@ -64,10 +64,11 @@ __device__ __forceinline__ void load_lds16(rsrc_t r, lds_void* lds, uint32_t vof
 constexpr uint32_t waitcnt_vm_lgkm0(uint32_t n) { return 0x0070u | n; }
 
 // ---------------------------------------------------------------------------
-// The attention tile body shared by the chunk-prefill and gathered-query
-// kernels: one wave's 32 query rows against 64-key K/V tiles held in LDS
-// (the attention of Sec. 3, "LLM Prefilling and Decoding", computed with an
-// online softmax).
+// The attention tile body of the gathered-query kernel: one wave's 32 query
+// rows against 64-key K/V tiles held in LDS (the attention of Sec. 3, "LLM
+// Prefilling and Decoding", computed with an online softmax).  The chunk
+// kernels have a body of their own (PipeTile) and take load_q and mask_half
+// from here.
 //
 //   * S^T = K Q^T with v_mfma_f32_32x32x16_bf16: a K fragment read from LDS is
 //     the A operand, the wave's Q rows (VGPRs, whole loop) the B operand.  In

@@ -28,7 +28,8 @@
 //     past the end) and loads each tensor's rows with the other lanes switched
 //     off.  Keys past the chunk end read as zero (out of range).  No copies.
 //   * Causal chunk: only tiles that reach past the first row of a wave run the
-//     mask on their logits.  With the bidirectional option (Eq. (4) read
+//     mask on their logits, and a wave computes up to its last row's last tile;
+//     from there it only takes part in the loads.  With the bidirectional option (Eq. (4) read
 //     literally: a chunk sees all of itself) every row's last key is the
 //     chunk's last key, so only the tile holding the chunk end is masked.
 //   * Work-groups are renumbered so that consecutive logical ids (the query

@@ -16,9 +16,8 @@
 //     rows per KV head, and a 32-token query 7*32 = 224 rows: one 256-row
 //     work-group of 8 waves reads each K/V tile once for all of them.
 //   * The tile body (MFMA S^T = K Q^T, online softmax, O^T = V^T P^T with the
-//     transposing LDS read, two 32-key halves) is WaveTile of attn_common.h,
-//     shared with the chunk prefill kernel.
-//   * Keys are walked in 64-key tiles, double-buffered in LDS.  A tile inside
+//     transposing LDS read, two 32-key halves) is WaveTile of attn_common.h.
+//   * Keys are walked in 64-key tiles, four buffers in LDS.  A tile inside
 //     the gathered region is loaded straight from HBM into LDS with a slot
 //     resolved per lane (the store is one buffer resource, so the rows of a
 //     tile may come from several segments); tiles inside the sink or the tail
@@ -186,7 +185,7 @@ __global__ __launch_bounds__(kGatherThreads, 1) void attn_gather_kernel(GatherAr
   const int t_lo = (int)((int64_t)n_tiles * part / a.parts);
   const int t_hi = (int)((int64_t)n_tiles * (part + 1) / a.parts);
 
-  // ---- tile loader (see the chunk prefill kernel for the LDS swizzles)
+  // ---- tile loader (LDS swizzles: lds_swz_k, lds_swz_v)
   const int rbytes = a.Hkv * D * 2;
   const rsrc_t rs_sk = make_rsrc(a.sink_k, S * rbytes), rs_sv = make_rsrc(a.sink_v, S * rbytes);
   const rsrc_t rs_gk = make_rsrc(a.store_k, a.cap * rbytes), rs_gv = make_rsrc(a.store_v, a.cap * rbytes);

@@ -31,9 +31,13 @@
 //     before the one that multiplies it; K and V fragments come from LDS (the
 //     compiler waits for those, also in front of assembly); settle() after
 //     every VALU write of O.
-//   * No divergent branch in the kernels around it: a register copy that the
-//     compiler puts at the join, before the lanes are switched on again,
-//     reaches only some of them.  Masks are selects; see load_tile_rows.
+//   * No divergent branch between the first and the last of these MFMAs: a
+//     register copy that the compiler puts at the join, before the lanes are
+//     switched on again, reaches only some of them.  Masks are selects, a tile's
+//     rows are loaded with the lanes switched off inside the assembly
+//     (load_tile_rows), and every other branch of the key loop is wave-uniform.
+//     The kernel's two branches on lanes lie outside: the zeroing of a V buffer
+//     before the loop (whole waves) and the stores after settle().
 #pragma once
 
 #include <type_traits>
